@@ -318,8 +318,8 @@ def cpu_baseline(layer, dt, inp, rows_req):
 
 
 KERNELS = {"wspec": "eqlinear_weight_spectrum (eql_wspec_kernel)",
-           "fwd": "eqlinear_forward (eql_gemm_kernel, forward)",
-           "dx": "eqlinear_backward_input (eql_gemm_kernel, input gradient)",
+           "fwd": "eqlinear_forward (eql_xs_kernel, forward)",
+           "dx": "eqlinear_backward_input (eql_xs_kernel, input gradient)",
            "dw": "eqlinear_backward_weight (eql_wgrad_kernel + eql_wgrad_reduce_kernel)",
            "bwd": "eqlinear_backward, single pass (eql_bwd_fused_kernel + eql_wgrad_reduce_kernel)"}
 

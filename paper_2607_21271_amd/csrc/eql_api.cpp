@@ -117,6 +117,146 @@ static WgradPlan wgrad_plan_rd(int64_t N, int T, int Cin, int Cout, bool w16) {
   return p;
 }
 
+// Plan of eql_xs_kernel.  The kernel runs 16 * RT rows a workgroup and NW waves
+// over its output tiles; what a plan trades:
+//   RT      row tiles share each weight fragment (the L1 path of the weight
+//           stream bounds wide 16-bit layers), at 4 T RT accumulators a lane
+//   osplit  more workgroups, each staging the rows again: for few rows, and for
+//           chunks, which keep every tile of a workgroup resident in a wave
+//   kc      steps staged at once: all of them, so that the waves are free to
+//           run to the end, or chunks where the spectrum of RT row tiles
+//           would leave one or two workgroups to a CU (or exceed the LDS);
+//           several small workgroups cover each other's staging
+// The lines below come from a sweep of RT, NW, osplit and kc over 183 problems
+// (T = 1 .. 16, 8 .. 1650 channels, 100 .. 400,000 rows, three types); the
+// choice is 1.06 times the sweep's best on average.  For instance (us, this
+// choice / other plans): T = 8, 384 -> 96, 12,608 rows, fp16: RT = 2, two
+// splits of three waves in chunks of 2 30.0 / one split of eight waves in
+// chunks of 6 33.4, all steps with RT = 1 41; T = 4, 768 -> 192, 25,216 rows,
+// fp16: RT = 4 in chunks of 4 76 / all steps 112; T = 4, 192 -> 768, fp16:
+// RT = 4 with eight waves 64 / RT = 2 with four 68; T = 4, 24 -> 96, 401,408
+// rows, fp16: RT = 4 with two waves 75 / with four 84; T = 8, 272 -> 16, 4,179
+// rows, fp32: chunks of 6 28 / all steps 44.
+XsPlan xs_plan(int64_t N, int T, int Ci, int Co, int dt, int cus) {
+  XsPlan p{};
+  const bool w16 = dt != kF32;
+  p.nks = xs_nks(Ci, w16);
+  const int kb = p.nks * T;  // KB of one row tile's spectrum
+  const int n_ot = (Co + 15) / 16;
+  const int64_t groups1 = (N + 15) / 16;
+  // row tiles: what the accumulators leave room for (fp32 is bound by its
+  // matrix rate, not by the weight stream)
+  const int rt_max = w16 && T <= 4 ? 4 : T <= 8 ? 2 : 1;
+  auto chunk = [&](int lim_kb, int rt) {  // even steps within lim_kb, or all
+    int kc = lim_kb / (rt * T) / 2 * 2;
+    if (kc < 2) kc = 2;
+    return kc < p.nks ? kc : p.nks;
+  };
+  p.kc = p.nks;
+  p.osplit = 1;
+  if (groups1 < 2 * cus) {
+    // few rows: the smallest estimate (microseconds) of the workgroup rounds
+    // times staging and product time of a workgroup beside those on its CU
+    const bool fft = T <= 4 || T == 8 || T == 16;
+    const double products = 1 + (T % 2 == 0) + 4 * ((T - 1) / 2);
+    double best = -1.0;
+    for (int rt = 1; rt <= (rt_max < 2 ? 1 : 2); ++rt) {
+      const int64_t groups = (N + 16 * rt - 1) / (16 * rt);
+      if (rt == 2 && groups * (n_ot < 8 ? n_ot : 8) < cus / 2) continue;
+      const double mfma = rt * products * (w16 ? 16 : 128);  // clocks of a tile and step
+      for (int nw = 2; nw <= 8; nw *= 2) {
+        for (int lim = 0; lim <= 64; lim += 32) {  // 0: all steps at once
+          const int kc = lim == 0 ? p.nks : chunk(lim, rt);
+          if (lim > 0 && kc == p.nks) continue;
+          const int lds = rt * kc * T;
+          if (lds > 150 || (nw == 8 && lds <= 30)) continue;
+          int occ = 160 / (lds < 8 ? 8 : lds);
+          if (occ > 12 / nw) occ = 12 / nw;
+          if (occ < 1) occ = 1;
+          const int chunks = (p.nks + kc - 1) / kc;
+          for (int os = 1, last = 0; os <= n_ot; ++os) {
+            const int per = (n_ot + os - 1) / os;
+            if (per == last) continue;
+            last = per;
+            if (kc < p.nks && per > nw) continue;
+            if (2 * per < nw && os > 1) break;
+            const int64_t wgs = groups * os;
+            const double rounds = (double)((wgs + (int64_t)cus * occ - 1) / ((int64_t)cus * occ));
+            const int64_t on_cu = (wgs + cus - 1) / cus;
+            const double conc = (double)(on_cu < occ ? on_cu : occ);
+            const int tiles = (per + nw - 1) / nw;
+            const double busy = conc * (per < nw ? per : nw);
+            const double stage = 0.5 + 0.6 * chunks +
+                                 rt * p.nks * (w16 ? 32 : 16) * 16.0 * T * (w16 ? 2 : 4) / (64.0 * nw) * 0.008 *
+                                     (1.0 + 0.3 * (conc - 1.0)) * (!fft && !w16 ? 2.0 : 1.0);
+            const double rate = mfma * (busy > 4.0 ? busy / 4.0 : 1.0) / 2200.0;   // matrix pipe
+            const double stream = 0.2 + 0.15 * T * 16.0 * busy / 2200.0;           // weights
+            const double t = rounds * (stage + tiles * (p.nks * (rate > stream ? rate : stream) + 0.3));
+            if (best < 0.0 || t < best) {
+              best = t;
+              p.RT = rt;
+              p.NW = nw;
+              p.osplit = os;
+              p.kc = kc;
+            }
+          }
+        }
+      }
+    }
+  } else {
+    int rt = rt_max;
+    if (!w16 && kb >= 24 && T <= 4) rt = 1;
+    if (n_ot <= 2 && rt > 1) rt = kb <= 24 ? 2 : 1;  // little to share: more, smaller workgroups
+    while (rt > 1 && N < (int64_t)24 * rt * cus * (w16 ? 1 : 2)) rt /= 2;
+    // KB of spectrum staged at once at most
+    const int whole = n_ot <= 2 ? 52 : T > 8 ? (n_ot <= 4 ? 64 : 100) : n_ot < 8 ? 64 : 100;
+    if (rt * kb <= whole || (rt > 2 && rt / 2 * kb <= 64 && n_ot <= 8 && n_ot > 2)) {
+      while (rt * kb > whole) rt /= 2;
+      const int lds = rt * kb;
+      p.NW = lds > 64 || (n_ot >= 16 && lds >= 56) ? 8 : 4;
+      if (n_ot <= 2) p.NW = lds < 20 ? 2 : 3;
+      else if (n_ot == 3) p.NW = 3;
+      else if ((n_ot == 5 || n_ot == 6) && lds <= 36)
+        p.NW = rt == 4 && lds <= 16 && (N + 63) / 64 >= 8 * (int64_t)cus ? 2 : 3;
+      if (!w16 && n_ot <= 3 && T >= 5) p.NW = 2;
+    } else if (n_ot <= 2) {
+      p.NW = 2;
+      p.kc = chunk(16, rt);
+    } else if (n_ot <= 8) {
+      p.osplit = n_ot <= 4 ? 1 : 2;
+      p.NW = (n_ot + p.osplit - 1) / p.osplit;
+      p.kc = chunk(40, rt);
+    } else {
+      const int per = n_ot <= 16 ? 4 : 8;
+      p.osplit = (n_ot + per - 1) / per;
+      p.NW = per;
+      p.kc = chunk(64, rt);
+    }
+    p.RT = rt;
+  }
+  // EQL_XS_PLAN=RT,NW,osplit,kc forces a plan where it is valid (tests, A/B
+  // timing); kc = 0 or at least the steps: all staged at once
+  if (const char* e = getenv("EQL_XS_PLAN")) {
+    int rt = 0, nw = 0, os = 0, kc = 0;
+    if (sscanf(e, "%d,%d,%d,%d", &rt, &nw, &os, &kc) == 4 && xs_rt_inst(T, rt) && nw >= 1 && nw <= 8 && os >= 1) {
+      if (os > n_ot) os = n_ot;
+      if (kc <= 0 || kc >= p.nks) kc = p.nks;
+      const int per = (n_ot + os - 1) / os;
+      if (rt * kc * T * 1024 + per * 64 <= kLdsBytes && (kc == p.nks || (kc % 2 == 0 && per <= nw))) {
+        p.RT = rt;
+        p.NW = nw;
+        p.osplit = os;
+        p.kc = kc;
+      }
+    }
+  }
+  // the bias of a workgroup's channels sits behind the spectrum
+  auto lds = [&] { return p.RT * p.kc * T * 1024 + ((n_ot + p.osplit - 1) / p.osplit) * 64; };
+  while (lds() > kLdsBytes && p.osplit < n_ot) p.osplit = 2 * p.osplit < n_ot ? 2 * p.osplit : n_ot;
+  p.lds_bytes = lds();
+  return p;
+}
+
 // Which weight-gradient kernel: EQL_WGRAD_KIND=0/1/2 forces one (tests, A/B timing).
 static int wgrad_forced_kind() {
   const char* v = getenv("EQL_WGRAD_KIND");
@@ -400,10 +540,6 @@ int launched(hipError_t e) { return e == hipSuccess ? EQL_OK : EQL_ERR_LAUNCH; }
 
 namespace eqk {
 // Read on every plan so that tests can switch it within one process.
-int gemm_forced_mode() {
-  const char* v = getenv("EQL_GEMM_MODE");
-  return (v != nullptr && v[0] >= '0' && v[0] <= '2' && v[1] == 0) ? v[0] - '0' : -1;
-}
 int gemm_big_forced() {
   const char* v = getenv("EQL_GEMM_BIG");
   return (v != nullptr && (v[0] == '0' || v[0] == '1') && v[1] == 0) ? v[0] - '0' : -1;
@@ -443,7 +579,7 @@ const char* eqlinear_status_string(int status) {
 
 size_t eqlinear_weight_spectrum_bytes(int T, int Cin, int Cout, int dtype) {
   if (check_shape(0, T, Cin, Cout, dtype) != EQL_OK) return 0;
-  const eqk::WspecDims d = eqk::wspec_dims(T, Cin, Cout, dtype != EQL_F32);
+  const eqk::WspecDims d = eqk::wspec_dims(Cin, Cout);
   const size_t bytes =
       (size_t)T * ((size_t)d.CoF * d.CiF + (size_t)d.CinB * d.CoutB) * elem_bytes(dtype);
   return bytes < ((size_t)1 << 31) ? bytes : 0;  // kernels address the spectrum with 31-bit offsets
@@ -483,7 +619,7 @@ static int gemm_common(const void* in, const void* wspec, const void* bias, void
   if (any_overlap(r, 4)) return EQL_ERR_INVALID_ARG;
   if ((st = check_device())) return st;
   if (N == 0) return EQL_OK;
-  const eqk::WspecDims d = eqk::wspec_dims(T, Cin, Cout, dtype != EQL_F32);
+  const eqk::WspecDims d = eqk::wspec_dims(Cin, Cout);
   const size_t fwd_block = (size_t)T * d.CoF * d.CiF * e;  // forward-layout planes
   if (eqk::gemm_big_choose(T, Ci, Co, dtype)) {
     eqk::BigArgs b{};
@@ -507,14 +643,15 @@ static int gemm_common(const void* in, const void* wspec, const void* bias, void
   a.Ci = Ci;
   a.Co = Co;
   a.stream = (hipStream_t)stream;
-  a.plan = eqk::gemm_plan(T, Ci, Co, dtype != EQL_F32);
-  eqk::gemm_plan_rows(a.plan, N, T, dtype != EQL_F32, eqk::device_cu_count());
+  a.plan = eqk::xs_plan(N, T, Ci, Co, dtype, eqk::device_cu_count());
   if (!bwd) {
     a.wsp = wspec;
     a.Ci_pad = d.CiF;
+    a.Co_pad = d.CoF;
   } else {
     a.wsp = (const char*)wspec + fwd_block;
     a.Ci_pad = d.CoutB;
+    a.Co_pad = d.CinB;
   }
   return launched(eqk::launch_gemm(dtype, T, bwd, a));
 }
@@ -685,7 +822,7 @@ int eqlinear_backward(const void* x, const void* dy, const void* wspec, void* dx
     return eqlinear_backward_weight(x, dy, dw, dbias, workspace, workspace_bytes, N, T, Cin, Cout, dtype,
                                     stream);
   }
-  const eqk::WspecDims d = eqk::wspec_dims(T, Cin, Cout, dtype != EQL_F32);
+  const eqk::WspecDims d = eqk::wspec_dims(Cin, Cout);
   eqk::FusedArgs a{};
   a.x = x;
   a.dy = dy;
@@ -908,7 +1045,6 @@ int eqlinear_gconv_forward(const void* f, const void* wspec, const void* bias, v
   if (any_overlap(r, 4)) return EQL_ERR_INVALID_ARG;
   if ((st = check_device())) return st;
   if (N == 0) return EQL_OK;
-  const bool w16 = dtype != EQL_F32;
   eqk::GemmArgs a{};
   a.in = f;
   a.wsp = wspec;
@@ -917,20 +1053,16 @@ int eqlinear_gconv_forward(const void* f, const void* wspec, const void* bias, v
   a.N = N;
   a.Ci = Ci;
   a.Co = Cout;
-  a.Ci_pad = eqk::wspec_dims(T, Ci, Cout, w16).CiF;
+  const eqk::WspecDims d = eqk::wspec_dims(Ci, Cout);
+  a.Ci_pad = d.CiF;
+  a.Co_pad = d.CoF;
   a.stream = (hipStream_t)stream;
   {
     const unsigned od = T == 4 ? (unsigned)(k / 2 + 1) : (unsigned)k;
     a.geo = eqk::GatherGeom{H, W, Cin, k, eqk::div_magic(W), eqk::div_magic(H), eqk::div_magic(Cin * T),
                             eqk::div_magic(od)};
   }
-  a.plan = eqk::gemm_plan(T, Ci, Cout, w16);
-  eqk::gemm_plan_rows(a.plan, N, T, w16, eqk::device_cu_count());
-  if (a.plan.narrow) return EQL_ERR_UNSUPPORTED;
-  if (a.plan.mode == 1) {  // the gathered rows are not kept resident: stream the weights
-    a.plan.mode = 0;
-    a.plan.lds_bytes = eqk::gemm_lds_c(T, w16, a.plan.OT, eqk::gemm_wblocks(0, a.plan.n_oc, a.plan.n_ks));
-  }
+  a.plan = eqk::xs_plan(N, T, Ci, Cout, dtype, eqk::device_cu_count());
   return launched(eqk::launch_gemm_gather(dtype, T, a));
 }
 

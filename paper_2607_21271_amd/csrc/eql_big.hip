@@ -19,7 +19,9 @@ hipError_t big_t(const BigArgs& a) {
   const int64_t n_rt = (a.N + kBigBM - 1) / kBigBM;
   const int bn = big_bn(GAUSS);
   const int n_ct = (a.Co + bn - 1) / bn;
-  if (n_rt * n_ct >= ((int64_t)1 << 31) || a.w_rows < a.Co || a.w_pitch < a.Ci) return hipErrorInvalidValue;
+  if (n_rt * n_ct >= ((int64_t)1 << 31) || a.w_rows < a.Co || a.w_pitch < a.Ci || a.w_rows % 32 != 0 ||
+      a.w_pitch % 32 != 0)
+    return hipErrorInvalidValue;
   hipLaunchKernelGGL(k, dim3((unsigned)(n_rt * n_ct)), dim3(kBigThreads), lds, a.stream, a.in, a.wsp, a.bias,
                      a.out, a.N, a.Ci, a.Co, a.w_rows, a.w_pitch, (int)n_rt, n_ct);
   return hipGetLastError();

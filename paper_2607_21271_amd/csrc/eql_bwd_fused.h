@@ -104,7 +104,7 @@ __global__ __launch_bounds__(512) void eql_bwd_fused_kernel(
       make_rsrc(reinterpret_cast<char*>(dx) + n_begin * rowx, (uint32_t)(len * rowx));
   constexpr int ITB = T * EB;  // bytes of one (row, channel)
 
-  // ---- weight spectrum, backward layout B[p][c][o] ([T][CinB][CoutB]), into
+  // ---- weight spectrum, the input gradient's copy ([T][CinB][CoutB]), into
   // LDS once: block (step s, plane p) holds rows c < C16 of the KR output
   // channels of step s, wl[(s*T + p)][c][KR], rows swizzled as the staging.
   {
@@ -124,7 +124,9 @@ __global__ __launch_bounds__(512) void eql_bwd_fused_kernel(
           const int c = rest % C16;
           const int sp = rest / C16;  // s * T + p
           const int p = sp % T, s = sp / T;
-          v[j] = *reinterpret_cast<const u32x4*>(wb + ((int64_t)(p * CinB + c) * CoutB + s * KR) * EB + chk * 16);
+          // fragment order (eql_xs.h): KR contraction channels are one step
+          const int64_t at = (((int64_t)(c >> 4) * (CoutB / KR) + s) * T + p) * 1024 + (chk * 16 + (c & 15)) * 16;
+          v[j] = *reinterpret_cast<const u32x4*>(wb + at);
           lo[j] = sp * C16 * RB + wl_off<RB>(c, chk * 16);
         }
       }

@@ -1,7 +1,7 @@
 // eql_gemm_big.h -- forward / input-gradient kernel for wide layers: large
 // output tiles for the MFMA-bound regime (fp16, bf16 and fp32).
 //
-// The same computation as eql_gemm_kernel (Alg. 1; Sec. 3.3-3.5: rDFT of the
+// The same computation as eql_xs_kernel (Alg. 1; Sec. 3.3-3.5: rDFT of the
 // activations in registers, per-bin products against the precomputed weight
 // spectrum with fp32 accumulation, irDFT and bias in the epilogue), laid out
 // for layers whose spectral products dominate the run time.  There the
@@ -13,8 +13,8 @@
 // (128 rows; two LDS buffers) and the weight spectrum (128 output channels;
 // three LDS buffers, loaded two steps ahead straight from global memory);
 // each wave reads four row fragments and four channel fragments per plane
-// and issues 16 MFMAs per product.  LDS operand traffic per MFMA is a quarter
-// of the 16-row tiles of eql_gemm_kernel.  Each step's barrier is an explicit
+// and issues 16 MFMAs per product.  Operand traffic per MFMA is a quarter of
+// that of one 16-row tile.  Each step's barrier is an explicit
 // wait plus s_barrier with compiler fences only, so loads of later steps stay
 // in flight across it.
 //
@@ -63,8 +63,8 @@ __device__ __forceinline__ void big_tile(int bid, int n_rt, int n_ct, int& rt, i
   ct = in / rows;
 }
 
-// in [N, Ci, T], weight spectrum planes [T][w_rows][w_pitch] (row = output
-// channel, w_pitch >= Ci padded with zeros), out [N, Co, T].  Requires
+// in [N, Ci, T], weight spectrum in fragment order (w_rows >= Co output and
+// w_pitch >= Ci contraction channels, zero padded), out [N, Co, T].  Requires
 // Ci % 32 == 0 and the per-tile row ranges below 2^31 bytes (host checks).
 // A step covers 64 bytes of each staged row: 32 channels of 16-bit elements
 // (v_mfma_f32_16x16x32_f16 / bf16), 16 of fp32 (four v_mfma_f32_16x16x4f32
@@ -131,21 +131,21 @@ void eql_gemm_big_kernel(const void* __restrict__ in, const void* __restrict__ w
     xoff[v] = (uint32_t)(row * rowb_in + q * UB);
     xlds[v] = wl_off<kBigRB>(row, q * HKW * EB);
   }
-  // weight chunks go from global memory straight into LDS (buffer_load ...
-  // lds): a wave-load writes 64 x 16 contiguous bytes (lane l at byte 16 l of
-  // the slice), so each lane fetches the chunk the swizzled layout puts at
-  // its slot
+  // weight blocks go from global memory straight into LDS (buffer_load ...
+  // lds): a wave-load moves one 1 KB block of the spectrum's fragment order
+  // (eql_xs.h), lane l its bytes 16 l .., which is also the LDS layout: block
+  // (plane, channel tile), read back as whole operands without conflicts
   constexpr int NWV = kBigThreads / 64;
+  constexpr int NTL = BN / 16;           // channel tiles of 16
   constexpr int WDU = WCH / (64 * NWV);  // wave-loads per wave and step
-  static_assert(WCH % (64 * NWV) == 0 && (BN * kBigRB) % 1024 == 0, "weight wave-loads");
+  static_assert(WCH % (64 * NWV) == 0 && WPL == NTL * 1024, "weight wave-loads");
+  const int nksw = w_pitch / BK;
   uint32_t woff[WDU];
 #pragma unroll
   for (int v = 0; v < WDU; ++v) {
-    const int slot = (v * NWV + wave) * 64 + lane;  // 16-byte slot of the weight planes
-    const int p = slot / (BN * 4), rem = slot - p * (BN * 4);
-    const int row = rem / 4, cs = rem % 4;
-    const int ch = cs ^ ((row >> 1) & 3);           // source chunk swizzled to slot cs
-    woff[v] = (uint32_t)(((int64_t)p * w_rows + o0 + row) * w_pitch * EB + ch * 16);
+    const int blk = v * NWV + wave;
+    const int p = blk / NTL, tl = blk - p * NTL;
+    woff[v] = (uint32_t)((((o0 >> 4) + tl) * nksw * T + p) * 1024 + lane * 16);
   }
 
   // Pipeline, per step s: the weight chunks of s + 2 issued into LDS buffer
@@ -168,7 +168,7 @@ void eql_gemm_big_kernel(const void* __restrict__ in, const void* __restrict__ w
   };
   auto load_w = [&](int s) __attribute__((always_inline)) {
 #if defined(__HIP_DEVICE_COMPILE__)
-    const int ws = s * BK * EB;
+    const int ws = s * (T * 1024);
     char* wl = wbase + (s % 3) * WB;
 #pragma unroll
     for (int v = 0; v < WDU; ++v)
@@ -265,7 +265,10 @@ void eql_gemm_big_kernel(const void* __restrict__ in, const void* __restrict__ w
     const char* wl = wbase + (s % 3) * WB;
     auto colf = [&](int p, FR (&Bp)[NJ]) __attribute__((always_inline)) {
 #pragma unroll
-      for (int j = 0; j < NJ; ++j) Bp[j] = lds_frag<16, kBigRB>(wl + p * WPL, wc * 16 * NJ + j * 16 + li, g);
+      for (int j = 0; j < NJ; ++j) {
+        const u32x4 a = *reinterpret_cast<const u32x4*>(wl + p * WPL + (wc * NJ + j) * 1024 + lane * 16);
+        Bp[j].w[0] = a[0]; Bp[j].w[1] = a[1]; Bp[j].w[2] = a[2]; Bp[j].w[3] = a[3];
+      }
     };
     auto rowf = [&](int p, int i) __attribute__((always_inline)) {
       return lds_frag<16, kBigRB>(xl + p * XPL, wr * 64 + i * 16 + li, g);

@@ -16,7 +16,7 @@ hipError_t Inst<T, DT>::wspec(const void* w, void* wspec, int Cin, int Cout, hip
 
 template <int T, int DT>
 hipError_t Inst<T, DT>::gemm(bool bwd, const GemmArgs& a) {
-  return bwd ? gemm_t<T, DT, true>(a) : gemm_t<T, DT, false>(a);
+  return bwd ? xs_t<T, DT, true>(a) : xs_t<T, DT, false>(a);
 }
 
 template <int T, int DT>

@@ -11,130 +11,30 @@ namespace eqk {
 
 inline int round_up(int v, int m) { return (v + m - 1) / m * m; }
 
-// Plan of the forward / input-gradient kernel for one direction (Ci -> Co).
-// Mirrors eql_gemm_kernel in eql_gemm.h: KW contraction channels per lane and
-// step; each wave of a pair computes OT output tiles of 16, so an o-chunk is
-// 32*OT channels.  Accumulators per lane (T*OT*4 floats) stay at or below 96
-// so two waves fit on each SIMD; the resident-spectrum variant uses half.
-struct GemmPlan {
-  int kw, kstep;   // channels per lane group and per step
-  int n_ks;        // contraction steps
-  int OT, OC;      // o-tiles per wave, channels per chunk
-  int n_oc;        // o-chunks
-  int mode;        // GemmMode: 0 streamed weights, 1 + resident spectrum, 2 resident weights
-  bool narrow;     // row stride not a multiple of the wide load: element loads, OT = 1, mode 0
-  int Co_pad;      // padded weight rows (n_oc * OC)
-  int lds_bytes;   // dynamic LDS of one workgroup
-};
 constexpr int kLdsBytes = 160 * 1024;
-// w16: 16-bit elements (fp16 or bf16), which share every shape and layout.
-constexpr int gemm_kw_c(int T, bool w16) {
-  const int fit = 128 / (T * (w16 ? 2 : 4));
-  if (w16) return fit >= 8 ? 8 : 4;
-  return fit >= 8 ? 8 : fit >= 4 ? 4 : fit >= 2 ? 2 : 1;
-}
-inline int gemm_kw(int T, bool w16) { return gemm_kw_c(T, w16); }
-constexpr int gemm_rb_c(int T, bool w16) { return 4 * gemm_kw_c(T, w16) * (w16 ? 2 : 4); }
-// LDS of one workgroup with n_wblocks weight blocks: two spectrum buffers of
-// 16*pairs*T rows and the blocks of 32*OT*T rows, each row RB bytes.
-constexpr int gemm_lds_c(int T, bool w16, int OT, int n_wblocks) {
-  return (2 * kGemmRoundRows * T + n_wblocks * 32 * OT * T) * gemm_rb_c(T, w16);
-}
-// o-tiles per wave: at most 96 accumulator floats per lane (T*OT*4), and two
-// weight blocks plus the spectrum buffers within the LDS.
-constexpr int gemm_otmax_c(int T, bool w16) {
-  const int by_acc = 24 / T > 8 ? 8 : (24 / T < 1 ? 1 : 24 / T);
-  int by_lds = 1;
-  while (by_lds < 8 && gemm_lds_c(T, w16, by_lds + 1, 2) <= kLdsBytes) ++by_lds;
-  return by_acc < by_lds ? by_acc : by_lds;
-}
-inline int gemm_otmax(int T, bool w16) { return gemm_otmax_c(T, w16); }
-inline int gemm_otres(int T, bool w16) {
-  return gemm_otmax(T, w16) / 2 < 1 ? 1 : gemm_otmax(T, w16) / 2;
-}
-// o-tile counts that have a kernel instantiation: 1, 2, 3, 4, 6, 8 up to the maximum.
-constexpr bool gemm_ot_inst(int T, bool w16, int OT) {
-  return OT >= 1 && OT <= gemm_otmax_c(T, w16) && (OT <= 4 || OT == 6 || OT == 8);
-}
-inline int gemm_ot_round(int T, bool w16, int want) {
-  for (int ot = want; ot <= gemm_otmax(T, w16); ++ot)
-    if (gemm_ot_inst(T, w16, ot)) return ot;
-  return gemm_otmax(T, w16);
-}
-// Widest activation load of one lane's run (KW/2 channels x T elements); the
-// row stride Ci*T*EB must be a multiple of it (eql_gemm.h GemmShape::WV).
-constexpr int gemm_wide_load_c(int T, bool w16) {
-  const int nbh = gemm_kw_c(T, w16) / 2 * T * (w16 ? 2 : 4);
-  return nbh % 16 == 0 ? 16 : nbh % 8 == 0 ? 8 : 4;
-}
-// Weight blocks held in LDS: two streamed blocks, two regions of n_ks blocks
-// (resident spectrum), or every block (resident weights).
-constexpr int gemm_wblocks(int mode, int n_oc, int n_ks) {
-  return mode == 2 ? n_oc * n_ks : mode == 1 ? 2 * n_ks : 2;
-}
-// EQL_GEMM_MODE=0/1/2 forces a weight mode where it is valid (tests, A/B timing).
-int gemm_forced_mode();
-inline GemmPlan gemm_plan(int T, int Ci, int Co, bool w16) {
-  GemmPlan p{};
-  p.kw = gemm_kw(T, w16);
-  p.kstep = 4 * p.kw;
-  p.n_ks = (Ci + p.kstep - 1) / p.kstep;
-  const int per_wave = ((Co + 15) / 16 + 1) / 2;  // o-tiles per wave for one chunk
-  const int otmax = gemm_otmax(T, w16);
-  // resident spectrum: two LDS regions of n_ks weight blocks each
-  const bool res_ok = T <= 8 && p.n_ks <= 3 && p.kw * (w16 ? 2 : 4) <= 16 &&
-                      gemm_lds_c(T, w16, gemm_otres(T, w16), 2 * p.n_ks) <= kLdsBytes;
-  if (per_wave <= otmax) {
-    p.OT = gemm_ot_round(T, w16, per_wave);
-    p.n_oc = 1;
-    p.mode = 0;
-  } else if (res_ok) {
-    p.OT = gemm_otres(T, w16);
-    p.n_oc = (Co + 32 * p.OT - 1) / (32 * p.OT);
-    p.mode = 1;
-  } else {
-    p.OT = otmax;
-    p.n_oc = (Co + 32 * otmax - 1) / (32 * otmax);
-    p.mode = 0;
-  }
-  // every weight block resident when they all fit
-  if (gemm_lds_c(T, w16, p.OT, p.n_oc * p.n_ks) <= kLdsBytes) p.mode = 2;
-  const int forced = gemm_forced_mode();
-  if (forced == 0 || (forced == 1 && res_ok && p.OT == gemm_otres(T, w16))) p.mode = forced;
-  p.narrow = ((int64_t)Ci * T * (w16 ? 2 : 4)) % gemm_wide_load_c(T, w16) != 0;
-  if (p.narrow) {
-    p.OT = 1;
-    p.n_oc = (Co + 31) / 32;
-    p.mode = 0;
-  }
-  p.OC = 32 * p.OT;
-  p.Co_pad = p.n_oc * p.OC;
-  p.lds_bytes = gemm_lds_c(T, w16, p.OT, gemm_wblocks(p.mode, p.n_oc, p.n_ks));
-  return p;
-}
 
-// Row-count adjustment at launch: resident weights pay for loading every block
-// up front, which only amortises when a workgroup runs several 64-row rounds;
-// with at most one round per CU the streamed mode overlaps that load with the
-// MFMAs.  Changes only the mode (never OT or the chunking), so the weight
-// spectrum layout is the same either way.
-inline void gemm_plan_rows(GemmPlan& p, int64_t N, int T, bool w16, int cus) {
-  if (p.mode == 2 && gemm_forced_mode() < 0 && N < (int64_t)2 * 64 * cus) {
-    p.mode = 0;
-    p.lds_bytes = gemm_lds_c(T, w16, p.OT, gemm_wblocks(0, p.n_oc, p.n_ks));
-  }
-}
-
-// Padded extents of the weight spectrum: rows to the o-chunks of the pass that
-// reads the layout, columns to 32 (a multiple of every contraction step).
+// Padded extents of the weight spectrum: rows and contraction channels to 32
+// (whole tiles of 16 rows, whole steps).
 constexpr int kColPad = 32;
 struct WspecDims {
   int CoF, CiF, CinB, CoutB;
 };
-inline WspecDims wspec_dims(int T, int Cin, int Cout, bool w16) {
-  return {gemm_plan(T, Cin, Cout, w16).Co_pad, round_up(Cin, kColPad),
-          gemm_plan(T, Cout, Cin, w16).Co_pad, round_up(Cout, kColPad)};
+inline WspecDims wspec_dims(int Cin, int Cout) {
+  const int ci = round_up(Cin, kColPad), co = round_up(Cout, kColPad);
+  return {co, ci, ci, co};
 }
+
+// Plan of eql_xs_kernel for Ci -> Co over N rows: row tiles per workgroup,
+// waves, output splits, steps, steps staged at once (all of them, or an even
+// chunk with at most NW output tiles per split) and the LDS.
+struct XsPlan {
+  int RT, NW, osplit, nks, kc, lds_bytes;
+};
+constexpr int xs_kf_c(bool w16) { return w16 ? 32 : 16; }  // contraction channels per step
+inline int xs_nks(int Ci, bool w16) { return (Ci + xs_kf_c(w16) - 1) / xs_kf_c(w16); }
+// row tiles that have an instantiation
+constexpr bool xs_rt_inst(int T, int RT) { return RT == 1 || (RT == 2 && T <= 8) || (RT == 4 && T <= 4); }
+XsPlan xs_plan(int64_t N, int T, int Ci, int Co, int dt, int cus);
 
 // Compute units of the current device (cached); 256 if unknown.
 int device_cu_count();
@@ -294,7 +194,8 @@ struct GemmArgs {
   void* out;
   int64_t N;
   int Ci, Co, Ci_pad;
-  GemmPlan plan;
+  int Co_pad;        // padded rows of the weights this pass reads
+  XsPlan plan;
   hipStream_t stream;
   GatherGeom geo;    // implicit patch gather only (else zero)
 };
@@ -355,7 +256,7 @@ struct BigArgs {
   void* out;
   int64_t N;
   int Ci, Co;        // contraction and output channels of this pass
-  int w_rows, w_pitch;  // rows (>= Co) and row pitch (>= Ci) of a spectrum plane
+  int w_rows, w_pitch;  // padded rows (>= Co) and contraction channels (>= Ci) of the spectrum
   hipStream_t stream;
 };
 constexpr int kBigMinC = 256;

@@ -1,20 +1,19 @@
 // eql_launch_impl.h -- tile choice and launches for one group order and element
 // type.  Included only by eql_inst.hip, which is compiled once per (T, dtype).
 #pragma once
-#include <mutex>
-
 #include "eql_gemm.h"
 #include "eql_kernels.h"
 #include "eql_wgrad.h"
 #include "eql_wgrad_rd.h"
 #include "eql_bwd_fused.h"
 #include "eql_launch.h"
+#include "eql_xs.h"
 
 namespace eqk {
 
 template <int T, int DT>
 hipError_t wspec_t(const void* w, void* wspec, int Cin, int Cout, hipStream_t s) {
-  const WspecDims d = wspec_dims(T, Cin, Cout, DT != kF32);
+  const WspecDims d = wspec_dims(Cin, Cout);
   const int omax = d.CoF > d.CoutB ? d.CoF : d.CoutB;  // tiles cover both layouts
   const int cmax = d.CiF > d.CinB ? d.CiF : d.CinB;
   constexpr int WO = 256 * (DT != kF32 ? 8 : 4) / kWsC;  // output channels per tile (eql_wspec_kernel)
@@ -24,109 +23,56 @@ hipError_t wspec_t(const void* w, void* wspec, int Cin, int Cout, hipStream_t s)
   return hipGetLastError();
 }
 
-// Resident workgroups per CU of one kernel at a given dynamic LDS size,
-// cached per (device, kernel, LDS).  The cache is shared by every host thread:
-// lookups and inserts hold one mutex (an entry never changes once written).
-inline int occupancy(const void* kernel, int threads, int lds) {
-  struct Entry { const void* k; int dev, lds, occ; };
-  static std::mutex mu;
-  static Entry cache[512];
-  static int n_cache = 0;
-  int dev = 0;
-  (void)hipGetDevice(&dev);
-  {
-    std::lock_guard<std::mutex> lock(mu);
-    for (int i = 0; i < n_cache; ++i)
-      if (cache[i].k == kernel && cache[i].dev == dev && cache[i].lds == lds) return cache[i].occ;
-  }
-  int occ = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kernel, threads, lds) != hipSuccess || occ <= 0) {
-    (void)hipGetLastError();
-    occ = 1;
-  }
-  std::lock_guard<std::mutex> lock(mu);
-  if (n_cache < 512) cache[n_cache++] = Entry{kernel, dev, lds, occ};
-  return occ;
-}
-
-// Persistent grid: one workgroup per resident slot (CUs x occupancy), and no
-// workgroup with fewer than 32 rows.
-inline int persistent_grid(const void* kernel, int threads, int lds, int64_t N, int64_t row_bytes) {
-  const int64_t slots = (int64_t)device_cu_count() * occupancy(kernel, threads, lds);
-  const int64_t by_rows = (N + 31) / 32;
-  int64_t g = slots < by_rows ? slots : by_rows;
-  if (g < 1) g = 1;
-  // each workgroup addresses its rows (plus one round of slack) with 31-bit offsets
-  while ((N / g + 65) * row_bytes >= ((int64_t)1 << 31)) g *= 2;
-  return (int)g;
-}
-
-template <int T, int DT, bool BWD, int OT, int MODE, int NKR, bool NARROW = false, bool GATHER = false>
-hipError_t gemm_variant(const GemmArgs& a) {
-  static_assert(GemmShape<T, DT>::WV == gemm_wide_load_c(T, DT != kF32), "host and kernel load widths");
-  auto k = eql_gemm_kernel<T, DT, BWD, OT, MODE, NKR, NARROW, GATHER>;
-  const int lds = a.plan.lds_bytes;
-  if (lds != gemm_lds_c(T, DT != kF32, OT, gemm_wblocks(MODE, a.plan.n_oc, a.plan.n_ks)) || lds > kLdsBytes ||
-      (MODE == kRes && a.plan.n_ks != NKR))
+template <int T, int DT, bool BWD, int RT, bool ODD, bool GATHER, bool CHUNK>
+hipError_t xs_variant(const GemmArgs& a) {
+  auto k = eql_xs_kernel<T, DT, BWD, RT, ODD, GATHER, CHUNK>;
+  const XsPlan& p = a.plan;
+  const bool w16 = DT != kF32;
+  const int nksw = a.Ci_pad / xs_kf_c(w16), w_tiles = a.Co_pad / 16, n_ot = (a.Co + 15) / 16;
+  // the kernel's assumptions: whole padded blocks, the spectrum of RT row
+  // tiles and the bias in LDS, rows of a workgroup below 2^31 bytes
+  if (p.nks != xs_nks(a.Ci, w16) || p.nks > nksw || a.Ci_pad % 32 != 0 || n_ot > w_tiles || p.osplit < 1 ||
+      p.osplit > n_ot || p.NW < 1 || p.NW > 8 || p.lds_bytes > kLdsBytes || p.kc < 1 ||
+      CHUNK != (p.kc < p.nks) || (CHUNK && (p.kc % 2 != 0 || (n_ot + p.osplit - 1) / p.osplit > p.NW)) ||
+      p.lds_bytes < RT * p.kc * T * 1024 + (BWD ? 0 : ((n_ot + p.osplit - 1) / p.osplit) * 64))
     return hipErrorInvalidValue;
-  if (lds > 64 * 1024) {
-    hipError_t e = hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+  if (p.lds_bytes > 64 * 1024) {
+    hipError_t e = hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, p.lds_bytes);
     if (e != hipSuccess) return e;
   }
-  // input and output rows are addressed with 31-bit offsets per workgroup
-  const int grid = persistent_grid((const void*)k, kGemmThreads, lds, a.N,
-                                   (int64_t)(a.Ci > a.Co ? a.Ci : a.Co) * T * (DT != kF32 ? 2 : 4));
-  hipLaunchKernelGGL(k, dim3((unsigned)grid), dim3(kGemmThreads), lds, a.stream, a.in, a.wsp, a.bias, a.out,
-                     a.N, a.Ci, a.Co, a.Ci_pad, a.plan.Co_pad, a.plan.n_oc, a.plan.n_ks, a.geo);
+  const int64_t groups = (a.N + 16 * RT - 1) / (16 * RT);
+  const int64_t blocks = (groups + 7) / 8 * 8 * p.osplit;
+  if (blocks >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k, dim3((unsigned)blocks), dim3(64 * p.NW), p.lds_bytes, a.stream, a.in, a.wsp, a.bias, a.out,
+                     a.N, a.Ci, a.Co, p.nks, nksw, p.kc, n_ot, p.osplit, w_tiles, a.geo);
   return hipGetLastError();
 }
 
-template <int T, int DT, bool BWD, int MODE, bool GATHER = false>
-hipError_t gemm_ot(const GemmArgs& a) {
+template <int T, int DT, bool BWD, bool GATHER = false>
+hipError_t xs_t(const GemmArgs& a) {
   hipError_t r = hipErrorInvalidValue;
-  static_for<8>([&](auto oi) {
-    constexpr int OT = decltype(oi)::value + 1;
-    if constexpr (gemm_ot_inst(T, DT != kF32, OT)) {
-      if (a.plan.OT == OT) r = gemm_variant<T, DT, BWD, OT, MODE, 0, false, GATHER>(a);
+  static_for<3>([&](auto ri) {
+    constexpr int RT = 1 << decltype(ri)::value;
+    if constexpr (xs_rt_inst(T, RT)) {
+      if (a.plan.RT != RT) return;
+      if constexpr (DT != kF32 && T % 2 == 1 && !GATHER) {
+        if (a.Ci % 2 != 0) {
+          r = a.plan.kc < a.plan.nks ? xs_variant<T, DT, BWD, RT, true, false, true>(a)
+                                       : xs_variant<T, DT, BWD, RT, true, false, false>(a);
+          return;
+        }
+      }
+      r = a.plan.kc < a.plan.nks ? xs_variant<T, DT, BWD, RT, false, GATHER, true>(a)
+                                   : xs_variant<T, DT, BWD, RT, false, GATHER, false>(a);
     }
   });
   return r;
 }
 
-// Forward with the implicit patch gather (group convolution, T in {1, 2,
-// 4}): the plan's mode is streamed or resident weights, never narrow loads.
+// Forward with the implicit patch gather (group convolution, T in {1, 2, 4}).
 template <int T, int DT>
 hipError_t gemm_gather_t(const GemmArgs& a) {
-  if constexpr (T == 1 || T == 2 || T == 4) {
-    const GemmPlan& p = a.plan;
-    if (p.narrow) return hipErrorInvalidValue;
-    if (p.mode == kStat) return gemm_ot<T, DT, false, kStat, true>(a);
-    if (p.mode == kStream) return gemm_ot<T, DT, false, kStream, true>(a);
-  }
-  return hipErrorInvalidValue;
-}
-
-template <int T, int DT, bool BWD>
-hipError_t gemm_t(const GemmArgs& a) {
-  constexpr int OTR = gemm_otmax_c(T, DT != kF32) / 2 < 1 ? 1 : gemm_otmax_c(T, DT != kF32) / 2;
-  constexpr bool kResOk = T <= 8 && GemmShape<T, DT>::FB <= 16;
-  const GemmPlan& p = a.plan;
-  if (p.narrow) {
-    if (p.OT != 1 || p.mode != kStream) return hipErrorInvalidValue;
-    return gemm_variant<T, DT, BWD, 1, kStream, 0, true>(a);
-  }
-  if (((int64_t)a.Ci * T * (DT != kF32 ? 2 : 4)) % GemmShape<T, DT>::WV != 0) return hipErrorInvalidValue;
-  if (p.mode == kRes) {
-    if constexpr (kResOk) {
-      if (p.OT != OTR) return hipErrorInvalidValue;
-      if (p.n_ks == 1) return gemm_variant<T, DT, BWD, OTR, kRes, 1>(a);
-      if (p.n_ks == 2) return gemm_variant<T, DT, BWD, OTR, kRes, 2>(a);
-      if (p.n_ks == 3) return gemm_variant<T, DT, BWD, OTR, kRes, 3>(a);
-    }
-    return hipErrorInvalidValue;
-  }
-  if (p.mode == kStat) return gemm_ot<T, DT, BWD, kStat>(a);
-  if (p.mode == kStream) return gemm_ot<T, DT, BWD, kStream>(a);
+  if constexpr (T == 1 || T == 2 || T == 4) return xs_t<T, DT, false, true>(a);
   return hipErrorInvalidValue;
 }
 

@@ -90,7 +90,7 @@ def passes_of(name, fused):
         return ["dw", "bwd"] if fused else ["dw"]
     if "wgrad" in name or "spec_rows" in name:
         return ["dw"]
-    if "gemm_kernel" in name or "gemm_big_kernel" in name:
+    if "xs_kernel" in name or "gemm_big_kernel" in name:
         targs = name.split("<")[1].split(">")[0].split(",")
         return ["dx"] if targs[2].strip() == "true" else ["fwd"]
     return []

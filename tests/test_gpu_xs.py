@@ -1,0 +1,61 @@
+"""GPU parity of the forward / input-gradient kernel (csrc/eql_xs.h) against the
+fp64 oracle in every form of its plan: one, two and four row tiles, all steps
+staged at once or in chunks (the last one odd), outputs split over workgroups,
+fewer and more waves than output tiles, channel counts off every tile and
+rows that start at half a word (16-bit types, odd T and odd channel counts).
+
+EQL_XS_PLAN=RT,NW,osplit,kc forces a plan where it is valid for the layer.  Bar
+as for the layer: max|gpu - oracle| / max|oracle| <= 1e-5 (fp32), 5e-3 (fp16),
+4e-2 (bf16).
+"""
+import pytest
+
+import synth
+from gpu_util import TOL, rel_err, run_gpu, say
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _need_gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+
+
+# (T, Cin, Cout, N, bias, plan)
+CASES = [(1, 33, 17, 130, True, "4,2,1,0"), (1, 160, 40, 67, False, "4,3,1,2"), (2, 70, 100, 65, True, "4,4,2,2"),
+         (3, 37, 53, 77, True, "4,2,1,0"), (3, 131, 35, 49, True, "2,4,1,2"), (4, 24, 96, 200, True, "4,2,1,0"),
+         (4, 135, 66, 70, True, "4,8,1,2"), (4, 200, 72, 33, False, "1,3,2,4"), (5, 37, 21, 100, True, "2,4,1,0"),
+         (5, 101, 50, 40, False, "2,4,1,2"), (7, 39, 53, 95, True, "2,3,2,0"), (7, 161, 18, 31, True, "1,2,1,4"),
+         (8, 96, 200, 50, True, "2,4,3,0"), (8, 170, 60, 47, False, "2,4,1,2"), (9, 65, 33, 45, True, "1,4,1,2"),
+         (12, 64, 50, 34, True, "1,8,1,0"), (13, 19, 35, 33, True, "1,1,1,0"), (15, 97, 40, 18, True, "1,3,1,2"),
+         (16, 48, 70, 17, True, "1,4,5,2"), (16, 64, 16, 1, True, "1,4,1,0")]
+
+
+@pytest.mark.parametrize("dt", ["f32", "f16", "bf16"])
+@pytest.mark.parametrize("T,Cin,Cout,N,bias,plan", CASES, ids=["T%d-%dx%d-N%d-%s-%s" % c for c in CASES])
+def test_forced_plans_match_oracle(orc, monkeypatch, T, Cin, Cout, N, bias, plan, dt):
+    say("xs plan", T, Cin, Cout, N, bias, plan, dt)
+    monkeypatch.setenv("EQL_XS_PLAN", plan)
+    inp = synth.draw(T, Cin, Cout, N, bias, 9950 + 17 * T + Cin + Cout).rounded(dt)
+    g = run_gpu(inp, dt, want=("y", "dx"))
+    errs = {"y": rel_err(g["y"], orc.forward(inp.x, inp.w, inp.b)),
+            "dx": rel_err(g["dx"], orc.backward_input(inp.dy, inp.w))}
+    say("  ", {k: "%.2e" % v for k, v in errs.items()})
+    for k, v in errs.items():
+        assert v <= TOL[dt], (k, v)
+
+
+@pytest.mark.parametrize("plan", ["2,4,1,0", "1,3,2,2", "4,2,1,4"])
+def test_plans_agree_bitwise(monkeypatch, plan):
+    """A plan only deals the work out: every one sums each output in the same
+    order, so the bits do not depend on it."""
+    inp = synth.draw(4, 140, 50, 333, True, 9990).rounded("f16")
+    monkeypatch.delenv("EQL_XS_PLAN", raising=False)
+    ref = run_gpu(inp, "f16", want=("y", "dx"))
+    monkeypatch.setenv("EQL_XS_PLAN", plan)
+    got = run_gpu(inp, "f16", want=("y", "dx"))
+    for k in ("y", "dx"):
+        assert (ref[k] == got[k]).all(), k
