@@ -96,10 +96,8 @@ __global__ __launch_bounds__(512) void eql_bwd_fused_kernel(
   // rows of this split as buffer ranges: bytes past the split read as zero,
   // stores past it are dropped
   const int rowx = Cin * T * EB, rowd = Cout * T * EB;
-  const __amdgpu_buffer_rsrc_t xrs =
-      make_rsrc(reinterpret_cast<const char*>(x) + n_begin * rowx, (uint32_t)(len * rowx));
-  const __amdgpu_buffer_rsrc_t drs =
-      make_rsrc(reinterpret_cast<const char*>(dy) + n_begin * rowd, (uint32_t)(len * rowd));
+  const RowRange xrs = make_rows<T, EB>(reinterpret_cast<const char*>(x) + n_begin * rowx, len * rowx);
+  const RowRange drs = make_rows<T, EB>(reinterpret_cast<const char*>(dy) + n_begin * rowd, len * rowd);
   const __amdgpu_buffer_rsrc_t dxrs =
       make_rsrc(reinterpret_cast<char*>(dx) + n_begin * rowx, (uint32_t)(len * rowx));
   constexpr int ITB = T * EB;  // bytes of one (row, channel)
@@ -195,6 +193,8 @@ __global__ __launch_bounds__(512) void eql_bwd_fused_kernel(
       if (NIX % 512 != 0 && item >= NIX) continue;
       int c, rp;
       wgrad_item<BC>(item, c, rp);
+      align_row<T, EB>(rx[R][u], 0, c);
+      align_row<T, EB>(rx[R][u], WPR, c + Cin);
       if constexpr (F16) {
         half2v P[T];
         transform_pair<T>(rx[R][u], P);
@@ -220,6 +220,8 @@ __global__ __launch_bounds__(512) void eql_bwd_fused_kernel(
       const int s = o / KR;
       const int ob = (o - s * KR) * EB;  // byte of o within its step's row
       char* const drs_base = dr + s * T * KR * RB;
+      align_row<T, EB>(rd[R][u], 0, o);
+      align_row<T, EB>(rd[R][u], WPR, o + Cout);
       if constexpr (F16) {
         half2v P[T];
         transform_pair<T>(rd[R][u], P);

@@ -127,40 +127,25 @@ __device__ __forceinline__ void store_run_rsrc(__amdgpu_buffer_rsrc_t rs, uint32
   }
 }
 
-// Raw bytes of one lane for one step: NB bytes at byte offset off (+ soff) of
-// the resource, with loads of W bytes (W = 2: 16-bit loads paired into words).
-// The width is a compile-time constant so that every kernel has a single load
-// shape: with the width chosen at run time among several load shapes feeding
-// the same registers, the register allocator in this toolchain produced code
-// that overwrote live raw words in some kernels.  Bytes past the resource
-// read as zero.
-template <int NB, int W>
-__device__ __forceinline__ void load_raw(__amdgpu_buffer_rsrc_t rs, uint32_t off, int soff,
-                                         uint32_t (&r)[NB / 4]) {
-  static_assert(NB % W == 0 && NB % 4 == 0, "load width");
-  if constexpr (W == 16) {
+// NW words from byte offset off (a multiple of 4) of the resource, in the widest
+// loads: a buffer load of two to four words needs word alignment only, and each
+// word past the resource reads as zero.  One load shape per kernel: with the
+// width chosen at run time among several load shapes feeding the same
+// registers, the register allocator in this toolchain produced code that
+// overwrote live raw words in some kernels.
+template <int NW>
+__device__ __forceinline__ void load_words(__amdgpu_buffer_rsrc_t rs, uint32_t off, uint32_t (&r)[NW]) {
+  constexpr int Q = NW / 4;
 #pragma unroll
-    for (int v = 0; v < NB / 16; ++v) {
-      const u32x4 x = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, off + 16 * v, soff, 0));
-      r[4 * v] = x[0]; r[4 * v + 1] = x[1]; r[4 * v + 2] = x[2]; r[4 * v + 3] = x[3];
-    }
-  } else if constexpr (W == 8) {
-#pragma unroll
-    for (int v = 0; v < NB / 8; ++v) {
-      const u32x2 x = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(rs, off + 8 * v, soff, 0));
-      r[2 * v] = x[0]; r[2 * v + 1] = x[1];
-    }
-  } else if constexpr (W == 4) {
-#pragma unroll
-    for (int v = 0; v < NB / 4; ++v) r[v] = __builtin_amdgcn_raw_buffer_load_b32(rs, off + 4 * v, soff, 0);
-  } else {
-#pragma unroll
-    for (int v = 0; v < NB / 4; ++v) {
-      const uint32_t lo = __builtin_amdgcn_raw_buffer_load_b16(rs, off + 4 * v, soff, 0);
-      const uint32_t hi = __builtin_amdgcn_raw_buffer_load_b16(rs, off + 4 * v + 2, soff, 0);
-      r[v] = (lo & 0xffffu) | (hi << 16);
-    }
+  for (int v = 0; v < Q; ++v) {
+    const u32x4 x = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, off + 16 * v, 0, 0));
+    r[4 * v] = x[0]; r[4 * v + 1] = x[1]; r[4 * v + 2] = x[2]; r[4 * v + 3] = x[3];
   }
+  if constexpr (NW % 4 >= 2) {
+    const u32x2 x = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(rs, off + 16 * Q, 0, 0));
+    r[4 * Q] = x[0]; r[4 * Q + 1] = x[1];
+  }
+  if constexpr (NW % 2 == 1) r[NW - 1] = __builtin_amdgcn_raw_buffer_load_b32(rs, off + 4 * (NW - 1), 0, 0);
 }
 
 // Zero the elements past nvalid (a ragged last channel group).

@@ -26,24 +26,52 @@
 
 namespace eqk {
 
-// The T elements of one (row, channel), EB bytes each, packed into words
-// (element e in half e%2 of word e/2 for 16-bit data).  Every (row, channel)
-// starts at a multiple of T*EB bytes, so the widest load width dividing T*EB
-// is always aligned; it is fixed at compile time (one load shape per kernel).
+// 16-bit elements and odd T: a (row, channel) starts at half a word when
+// row * channels + channel is odd.  (T = 1: one two-byte load a row, no words
+// to align.)
 template <int T, int EB>
-__device__ __forceinline__ void load_row(__amdgpu_buffer_rsrc_t rs, uint32_t off,
-                                         uint32_t (&w)[(T * EB + 3) / 4]) {
-  constexpr int NB = T * EB;
-  if constexpr (NB % 4 == 0) {
-    constexpr int W = NB % 16 == 0 ? 16 : NB % 8 == 0 ? 8 : 4;
-    load_raw<NB, W>(rs, off, 0, w);
+constexpr bool kHalfRows = EB == 2 && T % 2 == 1 && T > 1;
+
+// Rows of one tensor as a buffer range: rows past it read as zero.  With half
+// rows the range ends on the word that holds the last element (inside the same
+// allocation granule), and load_row drops the rows past it itself.
+struct RowRange {
+  __amdgpu_buffer_rsrc_t rs;
+  uint32_t bytes;
+};
+template <int T, int EB>
+__device__ __forceinline__ RowRange make_rows(const void* p, int64_t bytes) {
+  return RowRange{make_rsrc(p, (uint32_t)(kHalfRows<T, EB> ? (bytes + 3) & ~(int64_t)3 : bytes)), (uint32_t)bytes};
+}
+
+// The words that hold the T elements of one (row, channel) at byte offset off,
+// packed (element e in half e % 2 of word e / 2 for 16-bit data).  Half rows
+// come as the (T + 1) / 2 aligned words around them; align_row, called where
+// they are used so that no load is waited for here, moves the elements into
+// place.  Two-byte loads, paired as they arrived, took T loads and a wait a row;
+// the whole weight gradient, fp16, us, before -> after: T = 3 / 5 / 7 / 9, 64 x
+// 64, 32,768 rows 29 -> 17, 42 -> 20, 56 -> 24, 69 -> 31; T = 5, 1568 x 256,
+// 11,041 rows 1424 -> 404; T = 11, 336 x 47, 14,226 rows 212 -> 95; T = 7, 37 x
+// 53, 5,003 rows 31 -> 17.
+template <int T, int EB>
+__device__ __forceinline__ void load_row(const RowRange& rr, uint32_t off, uint32_t (&w)[(T * EB + 3) / 4]) {
+  if constexpr (T * EB == 2) {
+    w[0] = __builtin_amdgcn_raw_buffer_load_b16(rr.rs, off, 0, 0);
   } else {
+    if constexpr (kHalfRows<T, EB>) off = off < rr.bytes ? off & ~3u : kDropOffset;
+    load_words<(T * EB + 3) / 4>(rr.rs, off, w);
+  }
+}
+// W words at r + at; odd: the row started at half a word (the high half of the
+// last word is not an element).
+template <int T, int EB, int NR>
+__device__ __forceinline__ void align_row(uint32_t (&r)[NR], int at, int odd) {
+  if constexpr (kHalfRows<T, EB>) {
+    constexpr int WPR = (T * EB + 3) / 4;
+    const uint32_t sh = (odd & 1) * 16;
 #pragma unroll
-    for (int q = 0; q < (NB + 3) / 4; ++q) {
-      const uint32_t lo = __builtin_amdgcn_raw_buffer_load_b16(rs, off + 4 * q, 0, 0);
-      const uint32_t hi = (4 * q + 2 < NB) ? __builtin_amdgcn_raw_buffer_load_b16(rs, off + 4 * q + 2, 0, 0) : 0u;
-      w[q] = (lo & 0xffffu) | (hi << 16);
-    }
+    for (int q = 0; q < WPR; ++q)
+      r[at + q] = __builtin_amdgcn_alignbit(q + 1 < WPR ? r[at + q + 1] : 0u, r[at + q], sh);
   }
 }
 
@@ -167,10 +195,8 @@ __global__ __launch_bounds__(512) void eql_wgrad_kernel(const void* __restrict__
 
   // rows of this split as buffer ranges: bytes past the split read as zero
   const int rowx = Cin * T * EB, rowd = Cout * T * EB;
-  const __amdgpu_buffer_rsrc_t xrs =
-      make_rsrc(reinterpret_cast<const char*>(x) + n_begin * rowx, (uint32_t)((n_end - n_begin) * rowx));
-  const __amdgpu_buffer_rsrc_t drs =
-      make_rsrc(reinterpret_cast<const char*>(dy) + n_begin * rowd, (uint32_t)((n_end - n_begin) * rowd));
+  const RowRange xrs = make_rows<T, EB>(reinterpret_cast<const char*>(x) + n_begin * rowx, (n_end - n_begin) * rowx);
+  const RowRange drs = make_rows<T, EB>(reinterpret_cast<const char*>(dy) + n_begin * rowd, (n_end - n_begin) * rowd);
   constexpr int ITB = T * EB;  // bytes of one (row, channel)
 
   uint32_t rx[UX][RAW], rd[UD][RAW];
@@ -231,6 +257,9 @@ __global__ __launch_bounds__(512) void eql_wgrad_kernel(const void* __restrict__
       if (NIX % 512 != 0 && item >= NIX) continue;
       int c, rp;
       wgrad_item<BC>(item, c, rp);
+      // (splits and chunks start at even rows)
+      align_row<T, EB>(rx[u], 0, ct * BC + c);
+      align_row<T, EB>(rx[u], WPR, ct * BC + c + Cin);
       if constexpr (DT == kF16) {
         half2v P[T];
         transform_pair<T>(rx[u], P);
@@ -258,6 +287,8 @@ __global__ __launch_bounds__(512) void eql_wgrad_kernel(const void* __restrict__
       if (NID % 512 != 0 && item >= NID) continue;
       int o, rp;
       wgrad_item<BO>(item, o, rp);
+      align_row<T, EB>(rd[u], 0, ot * BO + o);
+      align_row<T, EB>(rd[u], WPR, ot * BO + o + Cout);
       if constexpr (DT == kF16) {
         half2v P[T];
         transform_pair<T>(rd[u], P);

@@ -69,9 +69,9 @@ __global__ __launch_bounds__(256) void eql_spec_rows_kernel(const void* __restri
   const int64_t n0 = rb * 64 + r8;
   const int64_t rows_here = N - rb * 64 < 64 ? N - rb * 64 : 64;
   // the block's rows as a buffer resource: rows past N read zero
-  const __amdgpu_buffer_rsrc_t rs =
-      make_rsrc(reinterpret_cast<const char*>(in) + rb * 64 * (int64_t)C * ITB,
-                (uint32_t)(rows_here > 0 ? rows_here * C * ITB : 0));
+  static_assert(!kHalfRows<T, EB>, "rows of whole words");
+  const RowRange rs = make_rows<T, EB>(reinterpret_cast<const char*>(in) + rb * 64 * (int64_t)C * ITB,
+                                rows_here > 0 ? rows_here * C * ITB : 0);
   const bool live = c < C;
   char* const o = reinterpret_cast<char*>(out);
   if constexpr (DT == kF32) {

@@ -91,24 +91,25 @@ __global__ __launch_bounds__(64 * NW) void eql_wgrad_rd_kernel(
   const int li = lane & 15;
 
   const int rowx = Cin * ITB, rowd = Cout * ITB;
-  const __amdgpu_buffer_rsrc_t xrs =
-      make_rsrc(reinterpret_cast<const char*>(x) + n_begin * rowx, (uint32_t)((n_end - n_begin) * rowx));
-  const __amdgpu_buffer_rsrc_t drs =
-      make_rsrc(reinterpret_cast<const char*>(dy) + n_begin * rowd, (uint32_t)((n_end - n_begin) * rowd));
+  const RowRange xrs = make_rows<T, EB>(reinterpret_cast<const char*>(x) + n_begin * rowx, (n_end - n_begin) * rowx);
+  const RowRange drs = make_rows<T, EB>(reinterpret_cast<const char*>(dy) + n_begin * rowd, (n_end - n_begin) * rowd);
 
   // Per-lane byte offsets of row 0 of the lane's rows in chunk 0, one per
   // block.  A channel past the tensor (tile padding) reads the last channel
   // instead: its sums land only in padded rows or columns of the partial,
   // which the reduction never reads.
   uint32_t boff[S::BLK];
+  int bch[S::BLK];  // the channel, for the half-word rows
 #pragma unroll
   for (int a = 0; a < CT; ++a) {
     const int c = min(ct * S::BC + 16 * a + li, Cin - 1);
+    bch[a] = c;
     boff[a] = (uint32_t)(((int64_t)RPL * g * Cin + c) * ITB);
   }
 #pragma unroll
   for (int b = 0; b < OT; ++b) {
     const int o = min(ot * S::BO + 16 * b + li, Cout - 1);
+    bch[CT + b] = o;
     boff[CT + b] = (uint32_t)(((int64_t)RPL * g * Cout + o) * ITB);
   }
 
@@ -120,7 +121,7 @@ __global__ __launch_bounds__(64 * NW) void eql_wgrad_rd_kernel(
   uint32_t raw[S::BLK][RAW];
   auto issue_block = [&](int bl, int chunk) __attribute__((always_inline)) {
     const bool isx = bl < CT;
-    const __amdgpu_buffer_rsrc_t rs = isx ? xrs : drs;
+    const RowRange& rs = isx ? xrs : drs;
     const uint32_t rstride = (uint32_t)(isx ? rowx : rowd);
     // rows past the split (the resource's end) read as zero; the host keeps
     // every offset below 2^31
@@ -157,6 +158,9 @@ __global__ __launch_bounds__(64 * NW) void eql_wgrad_rd_kernel(
         uint32_t two[2 * WPR];
 #pragma unroll
         for (int q = 0; q < 2 * WPR; ++q) two[q] = raw[bl][2 * m * WPR + q];
+        // (splits, chunks and a lane's rows start at even rows)
+        align_row<T, EB>(two, 0, bch[bl]);
+        align_row<T, EB>(two, WPR, bch[bl] + (bl < CT ? Cin : Cout));
         float P0[T], P1[T];
         transform_pair_f32<T>(two, P0, P1);
         dbs += P0[0] + P1[0];
@@ -169,6 +173,9 @@ __global__ __launch_bounds__(64 * NW) void eql_wgrad_rd_kernel(
         uint32_t two[2 * WPR];
 #pragma unroll
         for (int q = 0; q < 2 * WPR; ++q) two[q] = raw[bl][2 * m * WPR + q];
+        // (splits, chunks and a lane's rows start at even rows)
+        align_row<T, EB>(two, 0, bch[bl]);
+        align_row<T, EB>(two, WPR, bch[bl] + (bl < CT ? Cin : Cout));
         half2v P[T];
         transform_pair<T>(two, P);
 #pragma unroll

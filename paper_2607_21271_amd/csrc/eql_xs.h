@@ -60,22 +60,6 @@ struct XsShape {
   static constexpr int GP = NG == 1 ? T : (GE(0) > T - GE(0) ? GE(0) : T - GE(0));  // planes of the larger group
 };
 
-// NW words from byte offset off (a multiple of 4) of the resource.
-template <int NW>
-__device__ __forceinline__ void load_words(__amdgpu_buffer_rsrc_t rs, uint32_t off, uint32_t (&r)[NW]) {
-  constexpr int Q = NW / 4;
-#pragma unroll
-  for (int v = 0; v < Q; ++v) {
-    const u32x4 x = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, off + 16 * v, 0, 0));
-    r[4 * v] = x[0]; r[4 * v + 1] = x[1]; r[4 * v + 2] = x[2]; r[4 * v + 3] = x[3];
-  }
-  if constexpr (NW % 4 >= 2) {
-    const u32x2 x = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(rs, off + 16 * Q, 0, 0));
-    r[4 * Q] = x[0]; r[4 * Q + 1] = x[1];
-  }
-  if constexpr (NW % 2 == 1) r[NW - 1] = __builtin_amdgcn_raw_buffer_load_b32(rs, off + 4 * (NW - 1), 0, 0);
-}
-
 // LDS slot (bytes within a fragment block) of lane (g, i) at step ks.
 __device__ __forceinline__ int xs_slot(int g, int i, int ks) { return (g * 16 + (i ^ (g | ((ks & 3) << 2)))) * 16; }
 
