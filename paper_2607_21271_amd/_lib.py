@@ -53,6 +53,8 @@ SIGNATURES = {
     "eqlinear_gconv_pack_weight_adjoint": (_i, [_vp, _vp, _i, _i, _i, _i, _i, _vp]),
     "eqlinear_gconv_unpack_weight": (_i, [_vp, _vp, _i, _i, _i, _i, _i, _vp]),
     "eqlinear_gconv_forward": (_i, [_vp, _vp, _vp, _vp, _i64, _i, _i, _i, _i, _i, _i, _i, _vp]),
+    "eqlinear_group_norm": (_i, [_vp, _vp, _vp, _vp, _i64, _i, _i, ctypes.c_float, _i, _vp]),
+    "eqlinear_attention": (_i, [_vp, _vp, _i64, _i, _i, _i, ctypes.c_float, _i, _vp]),
 }
 
 
@@ -175,3 +177,11 @@ def eqlinear_gconv_unpack_weight(dw_ct, dpsi, T, Cin, Cout, k, dtype, stream) ->
 
 def eqlinear_gconv_forward(f, wspec, bias, y, B, H, W, T, Cin, Cout, k, dtype, stream) -> int:
     return lib().eqlinear_gconv_forward(f, wspec, bias, y, B, H, W, T, Cin, Cout, k, dtype, stream)
+
+
+def eqlinear_group_norm(x, weight, bias, y, rows, T, C, eps, dtype, stream) -> int:
+    return lib().eqlinear_group_norm(x, weight, bias, y, rows, T, C, eps, dtype, stream)
+
+
+def eqlinear_attention(qkv, o, B, L, heads, head_dim, scale, dtype, stream) -> int:
+    return lib().eqlinear_attention(qkv, o, B, L, heads, head_dim, scale, dtype, stream)

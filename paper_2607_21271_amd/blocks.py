@@ -29,7 +29,8 @@ from __future__ import annotations
 import torch
 import torch.nn.functional as F
 
-from .ops import EQLinear
+from . import _lib
+from .ops import _DT, EQLinear, _ptr, _stream
 
 
 class NaiveEQLinear(torch.nn.Module):
@@ -76,6 +77,27 @@ def _wide(t):
     return t.float() if t.dtype in (torch.float16, torch.bfloat16) else t
 
 
+def _inference(*ts) -> bool:
+    """Whether an operation on these tensors may run as one of the library's
+    kernels: plain tensors of one supported type on the current GPU, whole
+    16-byte words, and nothing that wants to see torch's own operations (a
+    gradient, autocast, tracing, a transform, a dispatch mode)."""
+    x = ts[0]
+    if not (x.is_cuda and x.dtype in _DT and x.numel() > 0 and x.device.index == torch.cuda.current_device()):
+        return False
+    for t in ts:
+        if not (type(t) in (torch.Tensor, torch.nn.Parameter) and t.dtype == x.dtype and t.device == x.device
+                and t.is_contiguous() and t.layout == torch.strided and not t.is_neg()):
+            return False
+        if t.requires_grad and torch.is_grad_enabled():
+            return False
+    return not (torch.is_autocast_enabled() or torch.jit.is_tracing() or torch.compiler.is_compiling()
+                or torch._C._functorch.peek_interpreter_stack() is not None
+                or torch.autograd.forward_ad._current_level >= 0
+                or torch._C._len_torch_dispatch_stack() > 0
+                or torch._C._len_torch_function_stack() > 0)
+
+
 class GroupLayerNorm(torch.nn.Module):
     """Layer norm over (C, T) with a per-channel affine map shared over T."""
 
@@ -86,6 +108,16 @@ class GroupLayerNorm(torch.nn.Module):
         self.bias = torch.nn.Parameter(torch.zeros(C, device=device, dtype=dtype))
 
     def forward(self, x):
+        if x.dim() >= 2 and x.shape[-2] == self.weight.numel() and _inference(x, self.weight, self.bias):
+            # rows of whole 16-byte words, at most 16 KB: one kernel in place of eleven passes
+            C, T = x.shape[-2:]
+            row = C * T * x.element_size()
+            if row % 16 == 0 and row <= 16384 and T <= 16 and x.data_ptr() % 16 == 0:
+                y = torch.empty_like(x)
+                _lib.check(_lib.eqlinear_group_norm(_ptr(x), _ptr(self.weight), _ptr(self.bias), _ptr(y),
+                                                    x.numel() // (C * T), T, C, self.eps, _DT[x.dtype],
+                                                    _stream(None)), "eqlinear_group_norm")
+                return y
         xf = _wide(x)
         mu = xf.mean(dim=(-2, -1), keepdim=True)
         var = (xf - mu).pow(2).mean(dim=(-2, -1), keepdim=True)
@@ -115,6 +147,14 @@ class EQViTBlock(torch.nn.Module):
     def attention(self, h):
         B, Lt, _, T = h.shape
         H, dh = self.heads, self.C // self.heads
+        # 16-bit elements, up to 256 tokens: one kernel in place of the three copies, two
+        # batched products and the scaled fp32 softmax between them
+        if (h.dtype != torch.float32 and dh * T in (32, 64, 128) and 1 <= Lt <= 256 and h.shape[2] == 3 * self.C
+                and H <= 512 and B <= 1 << 20 and _inference(h) and h.data_ptr() % 16 == 0):
+            o = torch.empty(B, Lt, self.C, T, dtype=h.dtype, device=h.device)
+            _lib.check(_lib.eqlinear_attention(_ptr(h), _ptr(o), B, Lt, H, dh * T, (dh * T) ** -0.5, _DT[h.dtype],
+                                               _stream(None)), "eqlinear_attention")
+            return o
         qkv = h.view(B, Lt, 3, H, dh * T).permute(2, 0, 3, 1, 4)   # [3, B, H, L, dh*T]
         q, k, v = (qkv[i].contiguous() for i in range(3))
         scores = torch.matmul(q, k.transpose(-1, -2).contiguous()) * (dh * T) ** -0.5

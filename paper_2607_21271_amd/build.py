@@ -23,7 +23,7 @@ BUILD_DIR = os.path.join(HERE, "_build")
 HOST_SOURCES = ["eql_api.cpp", "eql_dispatch.cpp"]
 MAX_T = 16
 # (source, object stem, extra defines)
-UNITS = [("eql_big.hip", "eql_big", [])] + [(s, os.path.splitext(s)[0], []) for s in HOST_SOURCES] + [
+UNITS = [("eql_big.hip", "eql_big", []), ("eql_block.hip", "eql_block", [])] + [(s, os.path.splitext(s)[0], []) for s in HOST_SOURCES] + [
     ("eql_inst.hip", "inst_%s_t%02d" % (name, t), ["-DEQK_T=%d" % t, "-DEQK_DT=%d" % dt])
     for t in range(MAX_T, 0, -1) for dt, name in ((1, "f16"), (0, "f32"), (2, "bf16"))]
 

@@ -1,4 +1,4 @@
-// eql_api.cpp -- the C ABI declared in include/eqlinear.h: argument checks,
+// eql_api.cpp -- the C ABI declared in include/eqlinear.h and eqlinear_block.h: argument checks,
 // device checks, workspace planning and dispatch to the gfx950 kernels.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -9,6 +9,7 @@
 #include <mutex>
 
 #include "../../include/eqlinear.h"
+#include "../../include/eqlinear_block.h"
 #include "eql_dihedral.h"
 #include "eql_gconv.h"
 #include "eql_launch.h"
@@ -1079,6 +1080,42 @@ int eqlinear_gconv_unpack_weight(const void* dw_ct, void* dpsi, int T, int Cin, 
 int eqlinear_gconv_pack_weight_adjoint(const void* psi, void* w_adj, int T, int Cin, int Cout, int k, int dtype,
                                        void* stream) {
   return gconv_common(4, psi, w_adj, 0, 0, 0, T, Cin, Cout, k, dtype, stream);
+}
+
+int eqlinear_group_norm(const void* x, const void* weight, const void* bias, void* y, int64_t rows, int T, int C,
+                        float eps, int dtype, void* stream) {
+  if (!valid_dtype(dtype) || T < 1 || C < 1 || rows < 0 || !weight || !bias) return EQL_ERR_INVALID_ARG;
+  if (rows > 0 && (!x || !y)) return EQL_ERR_INVALID_ARG;
+  const size_t e = elem_bytes(dtype);
+  if (T > EQLINEAR_MAX_T || C > kMaxC || rows > kMaxN || (size_t)C * T * e > (size_t)eqk::kNormMaxBytes ||
+      (size_t)C * T * e % 16 != 0)
+    return EQL_ERR_UNSUPPORTED;
+  if ((x && !aligned(x, 16)) || (y && !aligned(y, 16)) || !aligned(weight, e) || !aligned(bias, e))
+    return EQL_ERR_ALIGNMENT;
+  const Range r[4] = {{x, (size_t)rows * C * T * e}, {y, (size_t)rows * C * T * e}, {weight, C * e}, {bias, C * e}};
+  for (int i = 0; i < 4; ++i)
+    if (i != 1 && overlaps(r[1], r[i])) return EQL_ERR_INVALID_ARG;
+  if (int st = check_device()) return st;
+  if (rows == 0) return EQL_OK;
+  return launched(eqk::launch_group_norm(dtype, x, weight, bias, y, rows, T, C, eps, eqk::device_cu_count(),
+                                         (hipStream_t)stream));
+}
+
+int eqlinear_attention(const void* qkv, void* o, int64_t B, int L, int heads, int head_dim, float scale, int dtype,
+                       void* stream) {
+  if (!valid_dtype(dtype) || B < 0 || L < 1 || heads < 1 || head_dim < 1 || !(scale > 0.0f)) return EQL_ERR_INVALID_ARG;
+  if (B > 0 && (!qkv || !o)) return EQL_ERR_INVALID_ARG;
+  if (dtype == EQL_F32 || L > eqk::kAttnMaxL || heads > kMaxC / 128 ||
+      (head_dim != 32 && head_dim != 64 && head_dim != 128) || B > ((int64_t)1 << 20))
+    return EQL_ERR_UNSUPPORTED;
+  if ((qkv && !aligned(qkv, 16)) || (o && !aligned(o, 16))) return EQL_ERR_ALIGNMENT;
+  const size_t ob = (size_t)B * L * heads * head_dim * 2;
+  const Range r[2] = {{qkv, 3 * ob}, {o, ob}};
+  if (any_overlap(r, 2)) return EQL_ERR_INVALID_ARG;
+  if (int st = check_device()) return st;
+  if (B == 0) return EQL_OK;
+  return launched(eqk::launch_attention(dtype, qkv, o, B, L, heads, head_dim, scale, eqk::device_cu_count(),
+                                        (hipStream_t)stream));
 }
 
 }  // extern "C"

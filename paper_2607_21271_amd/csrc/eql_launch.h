@@ -281,4 +281,15 @@ hipError_t launch_wgrad(int dt, int T, const WgradArgs& a, const WgradPlan& p);
 hipError_t launch_wgrad_big(int dt, int T, const WgradArgs& a, const WgradPlan& p);
 hipError_t launch_bwd_fused(int dt, int T, const FusedArgs& a, const FusedPlan& p);
 
+// Encoder block kernels (eql_block.h): a layer-norm row of whole 16-byte
+// vectors, at most four a lane of a 256-thread workgroup; attention over at
+// most 256 tokens (the scores of a query tile stay in registers, K and V^T of a
+// head in LDS).
+constexpr int kNormMaxBytes = 4 * 256 * 16;
+constexpr int kAttnMaxL = 256;
+hipError_t launch_group_norm(int dt, const void* x, const void* w, const void* b, void* y, int64_t rows, int T, int C,
+                             float eps, int cus, hipStream_t stream);
+hipError_t launch_attention(int dt, const void* qkv, void* o, int64_t B, int L, int H, int D, float scale, int cus,
+                            hipStream_t stream);
+
 }  // namespace eqk
