@@ -208,13 +208,30 @@ XsPlan xs_plan(int64_t N, int T, int Ci, int Co, int dt, int cus) {
     int rt = rt_max;
     if (!w16 && kb >= 24 && T <= 4) rt = 1;
     if (n_ot <= 2 && rt > 1) rt = kb <= 24 ? 2 : 1;  // little to share: more, smaller workgroups
-    while (rt > 1 && N < (int64_t)24 * rt * cus * (w16 ? 1 : 2)) rt /= 2;
-    // KB of spectrum staged at once at most
-    const int whole = n_ot <= 2 ? 52 : T > 8 ? (n_ot <= 4 ? 64 : 100) : n_ot < 8 ? 64 : 100;
-    if (rt * kb <= whole || (rt > 2 && rt / 2 * kb <= 64 && n_ot <= 8 && n_ot > 2)) {
-      while (rt * kb > whole) rt /= 2;
+    // (a spectrum that one row tile already makes large, with many output tiles:
+    // two at any N; T = 8, 256 -> 512, 12,000 rows 82 / 70 us)
+    while (rt > 1 && N < (int64_t)24 * rt * cus * (w16 ? 1 : 2) && !(w16 && rt == 2 && T > 4 && n_ot > 16 && kb > 50))
+      rt /= 2;
+    // KB of spectrum staged at once at most, as it is and with half the row
+    // tiles.  16-bit layers of many output tiles read each staged row so often
+    // that one workgroup of eight waves a CU with all steps staged beats chunks,
+    // which stage the rows again for every split (us, chunks / all steps, inputs
+    // from HBM): T = 2, 512 -> 240, 60,000 rows 98 / 71; T = 2, 400 -> 160, 60,000
+    // rows 68 / 49; T = 4, 256 -> 240, 40,000 rows, bf16 77 / 55; T = 3, 320 ->
+    // 512, 30,000 rows 105 / 78; T = 8, 224 -> 384, 40,000 rows 178 / 150; T = 8,
+    // 256 -> 512, 12,000 rows 82 / 70.  With 9 to 12 output tiles 128 KB are level
+    // (T = 4, 512 -> 192 75 / 75; 400 -> 160 58 / 59).
+    const bool wide = w16 && T <= 8;
+    const int whole = n_ot <= 2 ? 52
+                      : T > 8   ? (n_ot <= 4 ? 64 : 100)
+                      : n_ot < 8 ? 64
+                      : wide && (n_ot > 16 || (rt == 2 && n_ot > 12)) ? 128 : 100;
+    const int half = n_ot <= 2 || (n_ot > 8 && !wide) ? 0 : n_ot > 12 && T > 1 ? 128 : 64;
+    const bool halve = rt * kb > whole && rt > 2 && rt / 2 * kb <= half;
+    if (rt * kb <= whole || halve) {
+      if (halve) rt /= 2;
       const int lds = rt * kb;
-      p.NW = lds > 64 || (n_ot >= 16 && lds >= 56) ? 8 : 4;
+      p.NW = lds > 64 || (n_ot >= 16 && lds >= 56) || (halve && n_ot > 8 && lds >= 48) ? 8 : 4;
       if (n_ot <= 2) p.NW = lds < 20 ? 2 : 3;
       else if (n_ot == 3) p.NW = 3;
       else if ((n_ot == 5 || n_ot == 6) && lds <= 36)
@@ -228,10 +245,14 @@ XsPlan xs_plan(int64_t N, int T, int Ci, int Co, int dt, int cus) {
       p.NW = (n_ot + p.osplit - 1) / p.osplit;
       p.kc = chunk(40, rt);
     } else {
-      const int per = n_ot <= 16 ? 4 : 8;
+      // three splits of four tiles, or of eight: four splits stage the rows four
+      // times (T = 4, 512 -> 240, 30,000 rows, bf16, splits of 4 / 8: 102 / 88; T =
+      // 2, 1024 -> 240, 40,000 rows 122 / 100; T = 1, 1536 -> 240, 60,000 rows in
+      // chunks of 16 / 8 steps 205 / 114)
+      const int per = n_ot <= (w16 ? 12 : 16) ? 4 : 8;
       p.osplit = (n_ot + per - 1) / per;
       p.NW = per;
-      p.kc = chunk(64, rt);
+      p.kc = chunk(w16 && T == 1 ? 32 : 64, rt);
     }
     p.RT = rt;
   }
