@@ -108,7 +108,7 @@ __global__ __launch_bounds__(256) void eql_group_norm_kernel(const void* __restr
 // It replaces three copies, two batched products and a scaled fp32 softmax
 // between them, which moved the score matrix through memory nine times.  Bound
 // by the exponentials and the staging; 128 images of 197 tokens, 12 heads of
-// 64, fp16: 49 us for 155 MB (3.2 TB/s) against about 800 us.  The norm and
+// 64, fp16: 49 us for 155 MB (3.2 TB/s) against about 680 us.  The norm and
 // this kernel together take the whole encoder block from 1576 to 430 us.
 constexpr int attn_k_pitch(int D) { return D * 2 + 16; }
 constexpr int attn_v_pitch(int KT) { return KT * 64 + 16; }
