@@ -53,10 +53,16 @@ hipError_t attn_kt(const void* qkv, void* o, int64_t B, int L, int H, float scal
     int64_t qs = (2 * (int64_t)cus + B * H - 1) / (B * H);
     const int max_qs = ((L + 15) / 16 + attn_waves(KT) - 1) / attn_waves(KT);
     if (qs > max_qs) qs = max_qs;
-    if (B * H * qs >= (int64_t)1 << 31) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k, dim3((unsigned)(B * H * qs)), dim3(attn_waves(KT) * 64), lds, stream, qkv, o, L, H,
-                       scale * 1.4426950408889634f, (int)qs);
-    return hipGetLastError();
+    const int64_t most = launch_blocks(attn_waves(KT) * 64) / (H * qs);  // images of one launch
+    for (int64_t b0 = 0; b0 < B; b0 += most) {
+      const int64_t n = B - b0 < most ? B - b0 : most;
+      hipLaunchKernelGGL(k, dim3((unsigned)(n * H * qs)), dim3(attn_waves(KT) * 64), lds, stream,
+                         (const char*)qkv + b0 * L * 6 * H * D, (char*)o + b0 * L * 2 * H * D, L, H,
+                         scale * 1.4426950408889634f, (int)qs);
+      const hipError_t e = hipGetLastError();
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
   }
 }
 

@@ -12,6 +12,9 @@ namespace eqk {
 inline int round_up(int v, int m) { return (v + m - 1) / m * m; }
 
 constexpr int kLdsBytes = 160 * 1024;
+// Workgroups of one launch: HIP refuses 2^32 threads and more, so a pass over
+// more rows than that takes several launches.
+constexpr int64_t launch_blocks(int threads) { return (((int64_t)1 << 32) - 1) / threads; }
 
 // Padded extents of the weight spectrum: rows and contraction channels to 32
 // (whole tiles of 16 rows, whole steps).

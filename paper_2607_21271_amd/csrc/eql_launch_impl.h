@@ -41,11 +41,16 @@ hipError_t xs_variant(const GemmArgs& a) {
     if (e != hipSuccess) return e;
   }
   const int64_t groups = (a.N + 16 * RT - 1) / (16 * RT);
-  const int64_t blocks = (groups + 7) / 8 * 8 * p.osplit;
-  if (blocks >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k, dim3((unsigned)blocks), dim3(64 * p.NW), p.lds_bytes, a.stream, a.in, a.wsp, a.bias, a.out,
-                     a.N, a.Ci, a.Co, p.nks, nksw, p.kc, n_ot, p.osplit, w_tiles, a.geo);
-  return hipGetLastError();
+  const int64_t most = launch_blocks(64 * p.NW) / p.osplit / 8 * 8;  // row groups of one launch
+  for (int64_t g0 = 0; g0 < groups; g0 += most) {
+    const int64_t n = groups - g0 < most ? groups - g0 : most;
+    hipLaunchKernelGGL(k, dim3((unsigned)((n + 7) / 8 * 8 * p.osplit)), dim3(64 * p.NW), p.lds_bytes, a.stream, a.in,
+                       a.wsp, a.bias, a.out, a.N, g0 * 16 * RT, a.Ci, a.Co, p.nks, nksw, p.kc, n_ot, p.osplit,
+                       w_tiles, a.geo);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 template <int T, int DT, bool BWD, bool GATHER = false>

@@ -79,11 +79,13 @@ constexpr int xs_raw_words(int T, bool w16, int RT, bool chunk) {
 // GATHER (forward of the group convolution, T in {1, 2, 4}): `in` is the
 // feature map f [N pixels, geo.Cin, T] and row n is the patch row of pixel n
 // (k*k*Cin channels: window orbits, then the centre), read straight from f.
-// nks: steps run; nksw: steps of the stored weights; w_tiles: their tiles.
+// row0: first row of this launch; nks: steps run; nksw: steps of the stored
+// weights; w_tiles: their tiles.
 template <int T, int DT, bool BWD, int RT, bool ODD, bool GATHER, bool CHUNK>
 __global__ __launch_bounds__(512, xs_waves(T, DT != kF32, RT, CHUNK)) void eql_xs_kernel(
     const void* __restrict__ in, const void* __restrict__ wsp, const void* __restrict__ bias, void* __restrict__ out,
-    int64_t N, int Ci, int Co, int nks, int nksw, int kc, int n_ot, int osplit, int w_tiles, GatherGeom geo) {
+    int64_t N, int64_t row0, int Ci, int Co, int nks, int nksw, int kc, int n_ot, int osplit, int w_tiles,
+    GatherGeom geo) {
   using S = XsShape<T, DT>;
   using Bn = Bins<T>;
   using FR = Frag<16>;
@@ -111,7 +113,7 @@ __global__ __launch_bounds__(512, xs_waves(T, DT != kF32, RT, CHUNK)) void eql_x
     os = j % osplit;
     rgp = (j / osplit) * 8 + (b & 7);
   }
-  const int64_t r0 = (int64_t)rgp * R;
+  const int64_t r0 = row0 + (int64_t)rgp * R;
   if (r0 >= N) return;
   const int len = N - r0 < R ? (int)(N - r0) : R;
   const int ot_lo = (int)((int64_t)os * n_ot / osplit), ot_hi = (int)((int64_t)(os + 1) * n_ot / osplit);
