@@ -958,10 +958,11 @@ int gconv_image(int64_t B, int H, int W) {
 
 template <typename E, int T, int K>
 void gconv_pixels(bool scatter, const void* in, void* out, int64_t n_pix, int H, int W, int Cin, hipStream_t s) {
-  // one wave per pixel, kGconvWaves pixels per block; past 2^30 blocks the
-  // kernels stride over the pixel groups
+  // one wave per pixel, kGconvWaves pixels per block; past the most blocks of
+  // a launch the kernels stride over the pixel groups
   const int64_t groups = (n_pix + eqk::kGconvWaves - 1) / eqk::kGconvWaves;
-  const dim3 grid((unsigned)(groups < ((int64_t)1 << 30) ? groups : ((int64_t)1 << 30)));
+  constexpr int64_t kMost = eqk::launch_blocks(64 * eqk::kGconvWaves);
+  const dim3 grid((unsigned)(groups < kMost ? groups : kMost));
   if (scatter)
     hipLaunchKernelGGL((eqk::eql_gconv_scatter_kernel<E, T, K>), grid, dim3(256), 0, s, (const E*)in, (E*)out,
                        n_pix, H, W, Cin);

@@ -1,5 +1,5 @@
 """More work than one launch can hold (2^32 threads) on the GPU: the forward, the input gradient and the encoder
-block's attention go on in a further launch, with the same results.
+block's attention go on in a further launch, the patch gather and its adjoint stride on, with the same results.
 
 One channel and one group element keep the tensors small (2 GiB each).  The layer is then y = w x + b, two roundings
 of fp16 (the spectrum of the weight is the weight); bound 2 u of the result, here on the first rows, on those around
@@ -58,3 +58,15 @@ def test_attention_of_several_launches():
     with torch.no_grad():
         o = blk.attention(qkv)
     assert torch.equal(o, qkv[:, :, 2 * C:])
+
+
+def test_patches_of_many_pixels():
+    """2^26 pixels, one wave each (a grid of 2^32 threads wraps to none): at k = 1 the patch is the pixel, gathered and
+    scattered back."""
+    from paper_2607_21271_amd import gconv
+    H, W = 8192, 8192
+    say("pixels", H * W)
+    f = torch.randn(1, H, W, 1, 1, device="cuda").to(torch.float16)
+    X = gconv.gather(f, 1, 1)
+    assert torch.equal(X.flatten(), f.flatten())
+    assert torch.equal(gconv.scatter(X, 1, H, W, 1, 1, 1), f)
