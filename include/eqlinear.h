@@ -67,7 +67,10 @@
 extern "C" {
 #endif
 
-#define EQLINEAR_ABI_VERSION 8
+/* Raised with every entry point added and every change to the contents of a
+ * buffer that a caller may keep (9: the weight spectrum in fragment order,
+ * eqlinear_block.h; a spectrum written by a library of version 8 is not read). */
+#define EQLINEAR_ABI_VERSION 9
 #define EQLINEAR_MAX_T 16
 
 typedef enum { EQL_F32 = 0, EQL_F16 = 1, EQL_BF16 = 2 } eql_dtype_t;

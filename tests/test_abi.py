@@ -45,6 +45,12 @@ def test_abi_version_matches_header(lib):
     assert L.eqlinear_abi_version() == int(m.group(1))
 
 
+def test_abi_version_tells_the_spectrum_layouts_apart(lib):
+    """The block entry points came with another order of the weight spectrum: a library that has them is not version 8,
+    whose spectra a caller may have kept."""
+    assert hasattr(lib, "eqlinear_group_norm") and L.eqlinear_abi_version() >= 9
+
+
 def test_status_strings(lib):
     seen = set()
     for s in range(8):
