@@ -108,7 +108,8 @@ class GroupLayerNorm(torch.nn.Module):
         self.bias = torch.nn.Parameter(torch.zeros(C, device=device, dtype=dtype))
 
     def forward(self, x):
-        if x.dim() >= 2 and x.shape[-2] == self.weight.numel() and _inference(x, self.weight, self.bias):
+        if (x.dim() >= 2 and _inference(x, self.weight, self.bias)
+                and self.weight.shape == self.bias.shape == x.shape[-2:-1]):
             # rows of whole 16-byte words, at most 16 KB: one kernel in place of eleven passes
             C, T = x.shape[-2:]
             row = C * T * x.element_size()

@@ -49,6 +49,31 @@ def test_group_norm(T, C, rows, dt):
     assert m(x.clone().requires_grad_(True)).requires_grad
 
 
+@pytest.mark.parametrize("shape", [(1,), (192, 1), (1, 192)])
+def test_group_norm_affine_of_another_shape(shape):
+    """A weight or bias that is not one value a channel keeps torch's broadcasting (the kernel reads C values of each):
+    a shared bias, and shapes that torch widens or refuses."""
+    from paper_2607_21271_amd.blocks import GroupLayerNorm
+    say("group norm affine", shape)
+    torch.manual_seed(5)
+    x = torch.randn(7, 192, 4, device="cuda")
+    for name in ("weight", "bias"):
+        m = GroupLayerNorm(192, device="cuda")
+        setattr(m, name, torch.nn.Parameter(torch.randn(shape, device="cuda"), requires_grad=False))
+        xd = x.double()
+        mu = xd.mean((-2, -1), keepdim=True)
+        n = (xd - mu) / ((xd - mu).square().mean((-2, -1), keepdim=True) + m.eps).sqrt()
+        with torch.no_grad():
+            try:
+                ref = n * m.weight.double()[:, None] + m.bias.double()[:, None]
+            except RuntimeError:
+                with pytest.raises(RuntimeError):
+                    m(x)
+                continue
+            y = m(x)
+        assert y.shape == ref.shape and _err(y, ref) <= TOL["f32"]
+
+
 @pytest.mark.parametrize("B,L,heads,D", [(1, 1, 1, 64), (2, 16, 3, 64), (1, 17, 2, 32), (3, 32, 1, 128), (2, 33, 5, 64),
                                          (1, 50, 12, 64), (2, 65, 3, 32), (1, 128, 2, 128), (1, 129, 2, 64),
                                          (5, 145, 6, 64), (50, 197, 12, 64), (1, 224, 3, 128), (2, 225, 2, 32),
