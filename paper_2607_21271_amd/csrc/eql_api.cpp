@@ -128,16 +128,16 @@ static WgradPlan wgrad_plan_rd(int64_t N, int T, int Cin, int Cout, bool w16) {
 //           run to the end, or chunks where the spectrum of RT row tiles
 //           would leave one or two workgroups to a CU (or exceed the LDS);
 //           several small workgroups cover each other's staging
-// The lines below come from a sweep of RT, NW, osplit and kc over 183 problems
-// (T = 1 .. 16, 8 .. 1650 channels, 100 .. 400,000 rows, three types); the
-// choice is 1.06 times the sweep's best on average.  For instance (us, this
-// choice / other plans): T = 8, 384 -> 96, 12,608 rows, fp16: RT = 2, two
-// splits of three waves in chunks of 2 30.0 / one split of eight waves in
-// chunks of 6 33.4, all steps with RT = 1 41; T = 4, 768 -> 192, 25,216 rows,
-// fp16: RT = 4 in chunks of 4 76 / all steps 112; T = 4, 192 -> 768, fp16:
-// RT = 4 with eight waves 64 / RT = 2 with four 68; T = 4, 24 -> 96, 401,408
-// rows, fp16: RT = 4 with two waves 75 / with four 84; T = 8, 272 -> 16, 4,179
-// rows, fp32: chunks of 6 28 / all steps 44.
+//   form    the pipelined form (eql_xs.h) where chunks would be staged for five
+//           or six output tiles at T = 8
+// The lines below come from sweeps of RT, NW, osplit and kc over some 900
+// problems (T = 1 .. 16, 8 .. 2368 channels, 100 .. 400,000 rows, three types),
+// inputs and outputs rotating through more memory than the caches hold; a time
+// in a comment is us at the stated size, other plan / this choice.  Against the
+// barrier-per-step kernel the choice is 1.7 times as fast on average (600 random
+// layers); some layers of few input channels and a width off 16 (T = 4, 8 -> 75,
+// 145,922 rows, bf16 28 / 37) and fp32 ones of T = 8 with two output tiles (48
+// -> 20, 94,288 rows 51 / 65) are slower.
 XsPlan xs_plan(int64_t N, int T, int Ci, int Co, int dt, int cus) {
   XsPlan p{};
   const bool w16 = dt != kF32;
@@ -207,11 +207,17 @@ XsPlan xs_plan(int64_t N, int T, int Ci, int Co, int dt, int cus) {
   } else {
     int rt = rt_max;
     if (!w16 && kb >= 24 && T <= 4) rt = 1;
-    if (n_ot <= 2 && rt > 1) rt = kb <= 24 ? 2 : 1;  // little to share: more, smaller workgroups
-    // (a spectrum that one row tile already makes large, with many output tiles:
-    // two at any N; T = 8, 256 -> 512, 12,000 rows 82 / 70 us)
-    while (rt > 1 && N < (int64_t)24 * rt * cus * (w16 ? 1 : 2) && !(w16 && rt == 2 && T > 4 && n_ot > 16 && kb > 50))
-      rt /= 2;
+    // (T = 8, 48 -> 32, 111,648 rows 96 / 78; 37 -> 48, 117,087 rows 138 / 99)
+    if (!w16 && ((T >= 5 && n_ot <= 3 && (T < 8 || p.nks > 1)) || (T <= 4 && n_ot <= 2 && kb >= 8))) rt = 1;
+    // a spectrum of few KB and little work a row: four row tiles, one or two
+    // waves (T = 1, 8 -> 32, 304,390 rows, bf16, four waves 17.5 / 11.4; T = 2, 16 ->
+    // 32, 164,161 rows, fp16, two row tiles and waves 13.3 / 11.5)
+    const bool tiny = T <= 2 && kb <= 4 && n_ot <= 2;
+    if (n_ot <= 2 && rt > 1 && !tiny) rt = kb <= 24 ? 2 : 1;  // little to share: more, smaller workgroups
+    // (two at any N with many output tiles: T = 8, 256 -> 512, 12,000 rows 82 / 70;
+    // T = 4, 48 -> 1125, 11,789 rows 39 / 35; 96 -> 768, 9,000 rows 27 / 24)
+    const bool keep2 = w16 && ((T > 4 && n_ot > 16 && kb > 50) || (T >= 4 && n_ot >= 40));
+    while (rt > 1 && N < (int64_t)24 * rt * cus * (w16 ? 1 : 2) && !(rt == 2 && keep2)) rt /= 2;
     // KB of spectrum staged at once at most, as it is and with half the row
     // tiles.  16-bit layers of many output tiles read each staged row so often
     // that one workgroup of eight waves a CU with all steps staged beats chunks,
@@ -221,29 +227,77 @@ XsPlan xs_plan(int64_t N, int T, int Ci, int Co, int dt, int cus) {
     // 512, 30,000 rows 105 / 78; T = 8, 224 -> 384, 40,000 rows 178 / 150; T = 8,
     // 256 -> 512, 12,000 rows 82 / 70.  With 9 to 12 output tiles 128 KB are level
     // (T = 4, 512 -> 192 75 / 75; 400 -> 160 58 / 59).
+    // fp32 of one or two output tiles: small chunks early (T = 4, 155 -> 16, 39,284
+    // rows 41 / 33; over 340 layers of T = 1 .. 4, 48 to 640 channels, the whole
+    // spectrum 1.12, these 1.03 times the best plan).
     const bool wide = w16 && T <= 8;
-    const int whole = n_ot <= 2 ? 52
+    const int whole = n_ot <= 2 ? (w16 || T > 8 ? 52 : T > 4 ? 32 : 16)
                       : T > 8   ? (n_ot <= 4 ? 64 : 100)
                       : n_ot < 8 ? 64
                       : wide && (n_ot > 16 || (rt == 2 && n_ot > 12)) ? 128 : 100;
     const int half = n_ot <= 2 || (n_ot > 8 && !wide) ? 0 : n_ot > 12 && T > 1 ? 128 : 64;
-    const bool halve = rt * kb > whole && rt > 2 && rt / 2 * kb <= half;
+    const bool halve = rt * kb > whole && rt > (w16 ? 2 : 1) && rt / 2 * kb <= half;
     if (rt * kb <= whole || halve) {
       if (halve) rt /= 2;
       const int lds = rt * kb;
       p.NW = lds > 64 || (n_ot >= 16 && lds >= 56) || (halve && n_ot > 8 && lds >= 48) ? 8 : 4;
+      // Waves.  A wave without a tile still stages, but takes registers from
+      // another workgroup: T = 12, 16 -> 24, 186,000 rows, fp16, four waves / two
+      // 29 / 27; T = 4, 24 -> 96, 401,408 rows, fp16 84 / 75, fp32 191 / 178; T = 8, 37
+      // -> 48, 117,087 rows, fp32 102 / 99 (three); T = 10, 48 -> 20, 27,198 rows,
+      // fp32, two / four 33 / 30 (staging without an FFT form); T = 4, 48 -> 402,
+      // 42,865 rows, bf16, four / eight 51 / 48 (rows off 16 channels); T = 4, 128 ->
+      // 81, 124,093 rows, fp32, three / four 190 / 173.
       if (n_ot <= 2) p.NW = lds < 20 ? 2 : 3;
       else if (n_ot == 3) p.NW = 3;
-      else if ((n_ot == 5 || n_ot == 6) && lds <= 36)
-        p.NW = rt == 4 && lds <= 16 && (N + 63) / 64 >= 8 * (int64_t)cus ? 2 : 3;
-      if (!w16 && n_ot <= 3 && T >= 5) p.NW = 2;
+      else if ((n_ot == 5 || n_ot == 6) && lds <= (w16 ? 36 : 24))
+        p.NW = (rt == 4 || !w16) && lds <= 16 && (N + 63) / 64 >= 8 * (int64_t)cus ? 2 : 3;
+      else if (w16 && rt == 4 && n_ot >= 24 && Co % 16 != 0) p.NW = 8;
+      if (!w16 && n_ot <= 2 && T >= 5) p.NW = T > 8 && kb > 28 && N >= 64 * (int64_t)cus ? 4 : 2;
+      if (tiny) p.NW = T == 1 || n_ot == 1 ? 1 : 2;
+      // one step and little work a row (T = 10, 16 -> 27, 89,862 rows 27.5 / 26.5; T =
+      // 16, 16 -> 48, 31,534 rows, bf16, three / one 24.9 / 18.6)
+      if (T > 8 && p.nks == 1 && w16 && (T <= 12 ? n_ot <= 2 && N >= 256 * (int64_t)cus : n_ot == 3)) p.NW = 1;
     } else if (n_ot <= 2) {
       p.NW = 2;
       p.kc = chunk(16, rt);
     } else if (n_ot <= 8) {
-      p.osplit = n_ot <= 4 ? 1 : 2;
-      p.NW = (n_ot + p.osplit - 1) / p.osplit;
-      p.kc = chunk(40, rt);
+      // Chunks of up to eight output tiles.  T = 8 with five or six: the pipelined
+      // form, unless its last round of workgroups would leave more than three
+      // eighths of the CUs idle (384 -> 96, fp16, chunks / pipelined: 12,608 rows
+      // 40 / 30, 8,200 33 / 27, 16,500 55 / 54, 50,432 123 / 111; bf16 12,608 42 / 34,
+      // 16,500 59 / 64).  Other 16-bit layers: two row tiles in four waves (T = 4, 384
+      // -> 96, 25,216 rows, bf16, four row tiles in three waves 53 / 37; 288 -> 96
+      // 41 / 31), four while one round holds them (T = 4, 576 -> 64, 25,088 rows 39 /
+      // 35; 35,088 rows 47 / 55), no idle fourth wave where all workgroups fit at
+      // once (T = 4, 384 -> 96, 12,608 rows 22 / 20).  fp32: one row tile, small
+      // chunks and splits of two or three tiles (T = 4, 384 -> 96, 25,216 rows 139 /
+      // 120; T = 8, 384 -> 96, 12,608 rows 165 / 153; T = 4, 384 -> 96, 12,608 rows 77 / 67).
+      const int64_t g64 = (N + 63) / 64, rounds = (g64 + cus - 1) / cus;
+      if (xs_pipe_inst(T, w16, 4) && n_ot >= 5 && n_ot <= 6 && (rounds == 1 || 8 * g64 >= 5 * rounds * cus)) {
+        p.form = kXsPipe;
+        rt = 4;
+        p.NW = 8;
+        p.kc = 1;
+      } else if (w16 && T <= 5) {
+        p.osplit = n_ot <= 4 ? 1 : 2;
+        if (rt == 4 && n_ot <= 4 && g64 <= 2 * cus) {
+          p.kc = chunk(64, rt);
+        } else {
+          if (rt > 2) rt = 2;
+          p.kc = chunk(T == 1 ? 16 : 40, rt);
+        }
+        p.NW = (N + 31) / 32 * p.osplit <= 4 * (int64_t)cus ? (n_ot + p.osplit - 1) / p.osplit : 4;
+      } else if (w16) {
+        p.osplit = n_ot <= 4 ? 1 : 2;
+        p.NW = (n_ot + p.osplit - 1) / p.osplit;
+        p.kc = chunk(40, rt);
+      } else {
+        rt = 1;
+        p.osplit = n_ot <= 4 ? 1 : n_ot <= 6 && T >= 5 ? 3 : 2;
+        p.NW = n_ot == 3 && T <= 4 ? 4 : (n_ot + p.osplit - 1) / p.osplit;
+        p.kc = chunk(n_ot == 5 || n_ot == 6 ? (T >= 5 ? 16 : 24) : 32, rt);
+      }
     } else {
       // three splits of four tiles, or of eight: four splits stage the rows four
       // times (T = 4, 512 -> 240, 30,000 rows, bf16, splits of 4 / 8: 102 / 88; T =
@@ -257,10 +311,21 @@ XsPlan xs_plan(int64_t N, int T, int Ci, int Co, int dt, int cus) {
     p.RT = rt;
   }
   // EQL_XS_PLAN=RT,NW,osplit,kc forces a plan where it is valid (tests, A/B
-  // timing); kc = 0 or at least the steps: all staged at once
+  // timing); kc = 0 or at least the steps: all staged at once; osplit = 0: the
+  // pipelined form
   if (const char* e = getenv("EQL_XS_PLAN")) {
     int rt = 0, nw = 0, os = 0, kc = 0;
-    if (sscanf(e, "%d,%d,%d,%d", &rt, &nw, &os, &kc) == 4 && xs_rt_inst(T, rt) && nw >= 1 && nw <= 8 && os >= 1) {
+    const bool read = sscanf(e, "%d,%d,%d,%d", &rt, &nw, &os, &kc) == 4;
+    if (read && os == 0) {
+      if (xs_pipe_inst(T, w16, rt) && kc >= 1 && kc <= p.nks && nw > n_ot && nw <= 8 &&
+          2 * rt * kc * T * 1024 + n_ot * 64 <= kLdsBytes && 16 * rt * kc * 8 <= xs_pipe_units(T) * 64 * (nw - n_ot)) {
+        p.RT = rt;
+        p.NW = nw;
+        p.osplit = 1;
+        p.kc = kc;
+        p.form = kXsPipe;
+      }
+    } else if (read && xs_rt_inst(T, rt) && nw >= 1 && nw <= 8 && os >= 1) {
       if (os > n_ot) os = n_ot;
       if (kc <= 0 || kc >= p.nks) kc = p.nks;
       const int per = (n_ot + os - 1) / os;
@@ -269,11 +334,15 @@ XsPlan xs_plan(int64_t N, int T, int Ci, int Co, int dt, int cus) {
         p.NW = nw;
         p.osplit = os;
         p.kc = kc;
+        p.form = kXsWhole;
       }
     }
   }
+  if (p.form != kXsPipe) p.form = p.kc < p.nks ? kXsChunk : kXsWhole;
   // the bias of a workgroup's channels sits behind the spectrum
-  auto lds = [&] { return p.RT * p.kc * T * 1024 + ((n_ot + p.osplit - 1) / p.osplit) * 64; };
+  auto lds = [&] {
+    return (p.form == kXsPipe ? 2 : 1) * p.RT * p.kc * T * 1024 + ((n_ot + p.osplit - 1) / p.osplit) * 64;
+  };
   while (lds() > kLdsBytes && p.osplit < n_ot) p.osplit = 2 * p.osplit < n_ot ? 2 * p.osplit : n_ot;
   p.lds_bytes = lds();
   return p;

@@ -30,13 +30,19 @@ inline WspecDims wspec_dims(int Cin, int Cout) {
 // Plan of eql_xs_kernel for Ci -> Co over N rows: row tiles per workgroup,
 // waves, output splits, steps, steps staged at once (all of them, or an even
 // chunk with at most NW output tiles per split) and the LDS.
+enum XsForm { kXsWhole = 0, kXsChunk = 1, kXsPipe = 2 };
 struct XsPlan {
   int RT, NW, osplit, nks, kc, lds_bytes;
+  int form;  // XsForm
 };
 constexpr int xs_kf_c(bool w16) { return w16 ? 32 : 16; }  // contraction channels per step
 inline int xs_nks(int Ci, bool w16) { return (Ci + xs_kf_c(w16) - 1) / xs_kf_c(w16); }
 // row tiles that have an instantiation
 constexpr bool xs_rt_inst(int T, int RT) { return RT == 1 || (RT == 2 && T <= 8) || (RT == 4 && T <= 4); }
+// the pipelined form: its instantiations, and the units of 4 channels a staging
+// thread holds (64 raw words)
+constexpr bool xs_pipe_inst(int T, bool w16, int RT) { return w16 && T == 8 && RT == 4; }
+constexpr int xs_pipe_units(int T) { return 64 / (2 * T); }
 XsPlan xs_plan(int64_t N, int T, int Ci, int Co, int dt, int cus);
 
 // Compute units of the current device (cached); 256 if unknown.

@@ -23,9 +23,9 @@ hipError_t wspec_t(const void* w, void* wspec, int Cin, int Cout, hipStream_t s)
   return hipGetLastError();
 }
 
-template <int T, int DT, bool BWD, int RT, bool ODD, bool GATHER, bool CHUNK>
+template <int T, int DT, bool BWD, int RT, bool ODD, bool GATHER, int FORM>
 hipError_t xs_variant(const GemmArgs& a) {
-  auto k = eql_xs_kernel<T, DT, BWD, RT, ODD, GATHER, CHUNK>;
+  auto k = eql_xs_kernel<T, DT, BWD, RT, ODD, GATHER, FORM>;
   const XsPlan& p = a.plan;
   const bool w16 = DT != kF32;
   const int nksw = a.Ci_pad / xs_kf_c(w16), w_tiles = a.Co_pad / 16, n_ot = (a.Co + 15) / 16;
@@ -33,14 +33,23 @@ hipError_t xs_variant(const GemmArgs& a) {
   // tiles and the bias in LDS, rows of a workgroup below 2^31 bytes
   if (p.nks != xs_nks(a.Ci, w16) || p.nks > nksw || a.Ci_pad % 32 != 0 || n_ot > w_tiles || p.osplit < 1 ||
       p.osplit > n_ot || p.NW < 1 || p.NW > 8 || p.lds_bytes > kLdsBytes || p.kc < 1 ||
-      CHUNK != (p.kc < p.nks) || (CHUNK && (p.kc % 2 != 0 || (n_ot + p.osplit - 1) / p.osplit > p.NW)) ||
-      p.lds_bytes < RT * p.kc * T * 1024 + (BWD ? 0 : ((n_ot + p.osplit - 1) / p.osplit) * 64))
+      FORM != p.form || (FORM != kXsPipe && (FORM == kXsChunk) != (p.kc < p.nks)) ||
+      (FORM == kXsChunk && (p.kc % 2 != 0 || (n_ot + p.osplit - 1) / p.osplit > p.NW)) ||
+      (FORM == kXsPipe && (p.osplit != 1 || n_ot >= p.NW ||
+                           16 * RT * p.kc * (xs_kf_c(w16) / 4) > xs_pipe_units(T) * 64 * (p.NW - n_ot))) ||
+      p.lds_bytes < (FORM == kXsPipe ? 2 : 1) * RT * p.kc * T * 1024 + (BWD ? 0 : ((n_ot + p.osplit - 1) / p.osplit) * 64))
     return hipErrorInvalidValue;
   if (p.lds_bytes > 64 * 1024) {
     hipError_t e = hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, p.lds_bytes);
     if (e != hipSuccess) return e;
   }
   const int64_t groups = (a.N + 16 * RT - 1) / (16 * RT);
+  if constexpr (FORM == kXsPipe) {  // one workgroup a CU, which walks its row groups
+    const int64_t cus = device_cu_count();
+    hipLaunchKernelGGL(k, dim3((unsigned)(groups < cus ? groups : cus)), dim3(64 * p.NW), p.lds_bytes, a.stream, a.in,
+                       a.wsp, a.bias, a.out, a.N, (int64_t)0, a.Ci, a.Co, p.nks, nksw, p.kc, n_ot, 1, w_tiles, a.geo);
+    return hipGetLastError();
+  }
   const int64_t most = launch_blocks(64 * p.NW) / p.osplit / 8 * 8;  // row groups of one launch
   for (int64_t g0 = 0; g0 < groups; g0 += most) {
     const int64_t n = groups - g0 < most ? groups - g0 : most;
@@ -58,17 +67,24 @@ hipError_t xs_t(const GemmArgs& a) {
   hipError_t r = hipErrorInvalidValue;
   static_for<3>([&](auto ri) {
     constexpr int RT = 1 << decltype(ri)::value;
+    constexpr bool pipe = xs_pipe_inst(T, DT != kF32, RT) && !GATHER;
+    if (a.plan.RT != RT) return;
+    if constexpr (pipe) {
+      if (a.plan.form == kXsPipe) {
+        r = xs_variant<T, DT, BWD, RT, false, false, kXsPipe>(a);
+        return;
+      }
+    }
     if constexpr (xs_rt_inst(T, RT)) {
-      if (a.plan.RT != RT) return;
       if constexpr (DT != kF32 && T % 2 == 1 && !GATHER) {
         if (a.Ci % 2 != 0) {
-          r = a.plan.kc < a.plan.nks ? xs_variant<T, DT, BWD, RT, true, false, true>(a)
-                                       : xs_variant<T, DT, BWD, RT, true, false, false>(a);
+          r = a.plan.form == kXsChunk ? xs_variant<T, DT, BWD, RT, true, false, kXsChunk>(a)
+                                      : xs_variant<T, DT, BWD, RT, true, false, kXsWhole>(a);
           return;
         }
       }
-      r = a.plan.kc < a.plan.nks ? xs_variant<T, DT, BWD, RT, false, GATHER, true>(a)
-                                   : xs_variant<T, DT, BWD, RT, false, GATHER, false>(a);
+      r = a.plan.form == kXsChunk ? xs_variant<T, DT, BWD, RT, false, GATHER, kXsChunk>(a)
+                                  : xs_variant<T, DT, BWD, RT, false, GATHER, kXsWhole>(a);
     }
   });
   return r;

@@ -59,3 +59,29 @@ def test_plans_agree_bitwise(monkeypatch, plan):
     got = run_gpu(inp, "f16", want=("y", "dx"))
     for k in ("y", "dx"):
         assert (ref[k] == got[k]).all(), k
+
+
+# The pipelined form: one turn and several a workgroup (16,384 rows are one turn of 256 CUs), a last chunk past the
+# channels, ragged rows and widths, one to five staging waves, chunks of one and two steps.
+PIPE_CASES = [(384, 96, 130, "4,8,0,1"), (70, 77, 64, "4,7,0,1"), (170, 90, 1, "4,8,0,1"), (33, 65, 16500, "4,8,0,1"),
+              (100, 96, 40007, "4,8,0,1"), (131, 50, 201, "4,8,0,2"), (96, 16, 99, "4,6,0,2"), (64, 80, 33000, "4,8,0,1")]
+
+
+@pytest.mark.parametrize("dt", ["f16", "bf16"])
+@pytest.mark.parametrize("kind", ["y", "dx"])
+@pytest.mark.parametrize("Ci,Co,N,plan", PIPE_CASES, ids=["%dx%d-N%d-%s" % c for c in PIPE_CASES])
+def test_pipelined_form(orc, monkeypatch, Ci, Co, N, plan, kind, dt):
+    """Same bits as a plan of one row tile that stages everything at once (every plan sums in the same order); the
+    oracle on the smaller ones."""
+    say("pipelined", Ci, Co, N, plan, kind, dt)
+    T = 8
+    Cin, Cout = (Ci, Co) if kind == "y" else (Co, Ci)
+    inp = synth.draw(T, Cin, Cout, N, True, 9900 + Ci + Co).rounded(dt)
+    monkeypatch.setenv("EQL_XS_PLAN", "1,4,1,0")
+    ref = run_gpu(inp, dt, want=(kind,))[kind]
+    monkeypatch.setenv("EQL_XS_PLAN", plan)
+    got = run_gpu(inp, dt, want=(kind,))[kind]
+    assert (got == ref).all()
+    if N <= 1000:
+        err = rel_err(got, orc.forward(inp.x, inp.w, inp.b) if kind == "y" else orc.backward_input(inp.dy, inp.w))
+        assert err <= TOL[dt], err

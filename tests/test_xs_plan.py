@@ -1,0 +1,71 @@
+"""Host plan of the forward / input-gradient kernel (csrc/eql_api.cpp, xs_plan), on the CPU.
+
+The plan is called in the built library by its C++ name.  Its choices on a 256-CU device: what the kernel assumes
+holds for every problem, and the forms that were measured to be the faster ones are taken.
+"""
+import ctypes
+import random
+
+import pytest
+
+from paper_2607_21271_amd import _lib
+
+WHOLE, CHUNK, PIPE = 0, 1, 2
+DT = {"f32": 0, "f16": 1, "bf16": 2}
+
+
+class Plan(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_int) for n in ("RT", "NW", "osplit", "nks", "kc", "lds_bytes", "form")]
+
+
+def plan(N, T, Ci, Co, dt, cus=256):
+    f = getattr(_lib.lib(), "_ZN3eqk7xs_planEliiiii")
+    f.restype = Plan
+    f.argtypes = [ctypes.c_int64] + [ctypes.c_int] * 5
+    return f(N, T, Ci, Co, DT[dt], cus)
+
+
+@pytest.fixture(autouse=True)
+def _own_plan(monkeypatch):
+    monkeypatch.delenv("EQL_XS_PLAN", raising=False)
+
+
+def test_plans_meet_the_kernels_assumptions():
+    rng = random.Random(3)
+    log = lambda a, b: int(round(a * (b / a) ** rng.random()))
+    for _ in range(30000):
+        T, dt, cus = rng.randint(1, 16), rng.choice(["f32", "f16", "bf16"]), rng.choice([256, 256, 304, 64, 1])
+        Ci, Co, N = log(1, 5000), log(1, 5000), log(1, 2000000)
+        p = plan(N, T, Ci, Co, dt, cus)
+        n_ot, w16 = (Co + 15) // 16, dt != "f32"
+        per = -(-n_ot // p.osplit)
+        at = (N, T, Ci, Co, dt, cus)
+        assert p.nks == -(-Ci // (32 if w16 else 16)) and 1 <= p.kc <= p.nks, at
+        assert p.RT in (1, 2, 4) and 1 <= p.NW <= 8 and 1 <= p.osplit <= n_ot, at
+        assert p.lds_bytes == (2 if p.form == PIPE else 1) * p.RT * p.kc * T * 1024 + per * 64 <= 160 * 1024, at
+        if p.form == PIPE:
+            assert w16 and T == 8 and p.RT == 4 and p.osplit == 1 and n_ot < p.NW, at
+            assert 16 * p.RT * p.kc * 8 <= 4 * 64 * (p.NW - n_ot), at  # staging units of a thread
+        else:
+            assert p.RT == 1 or T <= (8 if p.RT == 2 else 4), at
+            assert (p.form == CHUNK) == (p.kc < p.nks), at
+            assert p.form == WHOLE or (p.kc % 2 == 0 and per <= p.NW), at
+
+
+@pytest.mark.parametrize("N,T,Ci,Co,dt,want", [
+    # one workgroup a CU that stages beside its products, unless its last round leaves most CUs idle
+    (12608, 8, 384, 96, "f16", (4, 8, 1, 1, PIPE)), (12608, 8, 384, 96, "bf16", (4, 8, 1, 1, PIPE)),
+    (8300, 8, 768, 96, "f16", (4, 8, 1, 1, PIPE)), (50432, 8, 300, 65, "bf16", (4, 8, 1, 1, PIPE)),
+    (16500, 8, 384, 96, "f16", (2, 3, 2, 2, CHUNK)), (12608, 8, 384, 64, "f16", (2, 4, 1, 2, CHUNK)),
+    # small chunks of two row tiles (16-bit), of one in splits of two or three tiles (fp32)
+    (25216, 4, 384, 96, "bf16", (2, 4, 2, 4, CHUNK)), (25216, 4, 288, 96, "f16", (2, 4, 2, 4, CHUNK)),
+    (12608, 4, 384, 96, "f16", (2, 3, 2, 4, CHUNK)), (25088, 4, 576, 64, "f16", (4, 4, 1, 4, CHUNK)),
+    (35088, 4, 576, 64, "f16", (2, 4, 1, 4, CHUNK)),
+    (25216, 4, 384, 96, "f32", (1, 3, 2, 6, CHUNK)), (12608, 8, 384, 96, "f32", (1, 2, 3, 2, CHUNK)),
+    (12608, 8, 192, 48, "f32", (1, 3, 1, 4, CHUNK)), (39284, 4, 155, 16, "f32", (1, 2, 1, 4, CHUNK)),
+    # little work a row: few waves
+    (304390, 1, 8, 32, "bf16", (4, 1, 1, 1, WHOLE)), (111648, 8, 48, 32, "f32", (1, 2, 1, 3, WHOLE)),
+    (401408, 4, 24, 96, "f32", (2, 2, 1, 2, WHOLE)), (401408, 4, 24, 96, "f16", (4, 2, 1, 1, WHOLE))])
+def test_measured_choices(N, T, Ci, Co, dt, want):
+    p = plan(N, T, Ci, Co, dt)
+    assert (p.RT, p.NW, p.osplit, p.kc, p.form) == want
