@@ -175,10 +175,10 @@ XsPlan xs_plan(int64_t N, int T, int Ci, int Co, int dt, int cus) {
           if (occ > 12 / nw) occ = 12 / nw;
           if (occ < 1) occ = 1;
           const int chunks = (p.nks + kc - 1) / kc;
-          for (int os = 1, last = 0; os <= n_ot; ++os) {
-            const int per = (n_ot + os - 1) / os;
-            if (per == last) continue;
-            last = per;
+          // every tiles-per-split once, at its smallest osplit
+          for (int os = 1, per = n_ot; per > 0; os = per > 1 ? (n_ot + per - 2) / (per - 1) : n_ot + 1) {
+            if (os > n_ot) break;
+            per = (n_ot + os - 1) / os;
             if (kc < p.nks && per > nw) continue;
             if (2 * per < nw && os > 1) break;
             const int64_t wgs = groups * os;

@@ -5,6 +5,7 @@ holds for every problem, and the forms that were measured to be the faster ones 
 """
 import ctypes
 import random
+import time
 
 import pytest
 
@@ -69,3 +70,33 @@ def test_plans_meet_the_kernels_assumptions():
 def test_measured_choices(N, T, Ci, Co, dt, want):
     p = plan(N, T, Ci, Co, dt)
     assert (p.RT, p.NW, p.osplit, p.kc, p.form) == want
+
+
+@pytest.mark.parametrize("N,T,Ci,Co,dt,want", [
+    (197, 8, 48, 48, "f16", (1, 4, 2, 2)), (197, 8, 48, 3072, "f16", (1, 4, 48, 2)),
+    (100, 4, 192, 768, "f32", (1, 8, 12, 12)), (1000, 16, 64, 64, "bf16", (1, 8, 1, 2)),
+    (5003, 7, 37, 53, "f16", (1, 4, 1, 2)), (129, 13, 64, 338, "bf16", (1, 4, 11, 2)),
+    (33, 4, 768, 4000, "f16", (1, 8, 63, 24)), (8000, 4, 96, 384, "f32", (2, 8, 1, 6)),
+    (700, 2, 1024, 1024, "f16", (2, 8, 11, 32)), (64, 8, 384, 96, "f16", (1, 8, 1, 12)),
+    (3000, 5, 500, 2000, "bf16", (2, 8, 16, 6)), (1, 1, 65536, 65536, "f32", (1, 8, 512, 64))])
+def test_few_row_choices(N, T, Ci, Co, dt, want):
+    """The plan of least estimated time over every output split."""
+    p = plan(N, T, Ci, Co, dt)
+    assert (p.RT, p.NW, p.osplit, p.kc) == want
+
+
+def test_few_row_search_does_not_grow_with_the_output_tiles():
+    """Every split that gives a workgroup as many tiles as another is tried once: 4,096 output tiles take less than ten
+    times three (5 with the search over distinct tile counts, 22 over every split)."""
+    def us(Co):
+        best = 1e9
+        for _ in range(7):
+            t0 = time.perf_counter()
+            for _ in range(300):
+                f(197, 8, 48, Co, 1, 256)
+            best = min(best, time.perf_counter() - t0)
+        return best
+
+    plan(197, 8, 48, 48, "f16")  # sets the signature
+    f = getattr(_lib.lib(), "_ZN3eqk7xs_planEliiiii")
+    assert us(65536) < 10 * us(48)
