@@ -310,11 +310,12 @@ XsPlan xs_plan(int64_t N, int T, int Ci, int Co, int dt, int cus) {
     }
     p.RT = rt;
   }
-  // EQL_XS_PLAN=RT,NW,osplit,kc forces a plan where it is valid (tests, A/B
-  // timing); kc = 0 or at least the steps: all staged at once; osplit = 0: the
-  // pipelined form
+  // EQL_XS_PLAN=RT,NW,osplit,kc forces a plan (tests, A/B timing); kc = 0 or at
+  // least the steps: all staged at once; osplit = 0: the pipelined form.  A plan
+  // that the layer cannot run fails the launch (no kernel has zero row tiles).
   if (const char* e = getenv("EQL_XS_PLAN")) {
     int rt = 0, nw = 0, os = 0, kc = 0;
+    p.RT = 0;
     const bool read = sscanf(e, "%d,%d,%d,%d", &rt, &nw, &os, &kc) == 4;
     if (read && os == 0) {
       if (xs_pipe_inst(T, w16, rt) && kc >= 1 && kc <= p.nks && nw > n_ot && nw <= 8 &&

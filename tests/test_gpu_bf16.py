@@ -79,20 +79,19 @@ MODES = [(3, 64, 64, 1029, True), (4, 24, 96, 2085, False), (8, 48, 48, 613, Tru
          (12, 64, 64, 257, True), (8, 96, 384, 300, False)]
 
 
-@pytest.mark.parametrize("mode", ["0", "1", "2"])
+@pytest.mark.parametrize("plan", ["1,2,1,0", "1,4,2,6", "1,8,3,2"])
 @pytest.mark.parametrize("T,Cin,Cout,N,bias", MODES, ids=["T%d-%dx%d-N%d" % f[:4] for f in MODES])
-def test_forced_weight_mode(orc, monkeypatch, T, Cin, Cout, N, bias, mode):
-    """Streamed (0), resident-spectrum (1, where the plan allows it) and
-    resident-weight (2, where the blocks fit) instantiations."""
-    say("forced mode", mode, T, Cin, Cout, N, DT)
-    monkeypatch.setenv("EQL_GEMM_MODE", mode)
+def test_forced_plan(orc, monkeypatch, T, Cin, Cout, N, bias, plan):
+    """All steps at once, chunks of six and of two steps, in one to three output splits."""
+    say("forced plan", plan, T, Cin, Cout, N, DT)
+    monkeypatch.setenv("EQL_XS_PLAN", plan)
     inp = synth.draw(T, Cin, Cout, N, bias, 7100 + 31 * T + Cin + Cout).rounded(DT)
     g = run_gpu(inp, DT, want=("y", "dx"))
     errs = {"y": rel_err(g["y"], orc.forward(inp.x, inp.w, inp.b)),
             "dx": rel_err(g["dx"], orc.backward_input(inp.dy, inp.w))}
     say("  ", {k: "%.2e" % v for k, v in errs.items()})
     for k, v in errs.items():
-        assert v <= TOL[DT], (T, Cin, Cout, mode, k, v)
+        assert v <= TOL[DT], (T, Cin, Cout, plan, k, v)
 
 
 KIND_CASES = [(8, 96, 384, 700, False), (4, 24, 96, 1111, False), (3, 64, 64, 517, True),

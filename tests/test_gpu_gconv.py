@@ -142,6 +142,39 @@ def test_implicit_gather_forward(go, B, H, W, T, Cin, Cout, k, bias, dt):
     assert err <= TOL[dt]
 
 
+# Row tiles, chunks and splits of the gathered staging, forced for the implicit call only: chunk offsets into the
+# window orbits, row tiles past the pixels, a last chunk of one step.
+GATHER_PLANS = ["1,4,1,0", "2,3,2,0", "4,4,1,0", "1,3,2,2", "2,4,2,4", "4,3,2,2"]
+
+
+@pytest.mark.parametrize("dt", ["f32", "f16", "bf16"])
+@pytest.mark.parametrize("plan", GATHER_PLANS)
+@pytest.mark.parametrize("B,H,W,T,Cin,Cout,k", [(1, 9, 7, 4, 16, 40, 3), (2, 5, 7, 2, 24, 20, 3), (1, 7, 19, 1, 32, 70, 3)])
+def test_implicit_gather_plans(monkeypatch, B, H, W, T, Cin, Cout, k, plan, dt):
+    from paper_2607_21271_amd import gconv, ops
+    say("gconv plan", B, H, W, T, Cin, Cout, k, plan, dt)
+    f, psi, b, _ = _draw(B, H, W, T, Cin, Cout, k, True, 8750 + T, dt)
+    ft, bt = to_dev(f, dt), to_dev(b, dt)
+    wspec = ops.weight_spectrum(gconv.pack_weight(to_dev(psi, dt)))
+    y_ref = ops.forward(gconv.gather(ft, T, k), wspec, bt, T, k * k * Cin, Cout).view(B, H, W, Cout, T)
+    monkeypatch.setenv("EQL_XS_PLAN", plan)
+    assert torch.equal(gconv.forward_implicit(ft, wspec, bt, T, Cout, k), y_ref)
+
+
+@pytest.mark.parametrize("Cin,Cout,dt", [(24, 24, "f32"), (64, 96, "f16"), (64, 64, "bf16")])
+def test_implicit_gather_in_chunks(Cin, Cout, dt):
+    """Enough pixels that the plan itself stages in chunks."""
+    from paper_2607_21271_amd import gconv, ops
+    from test_xs_plan import CHUNK, plan
+    B, H, W, T, k = 2, 64, 66, 4, 3
+    assert plan(B * H * W, T, k * k * Cin, Cout, dt).form == CHUNK
+    f, psi, b, _ = _draw(B, H, W, T, Cin, Cout, k, True, 8790, dt)
+    ft, bt = to_dev(f, dt), to_dev(b, dt)
+    wspec = ops.weight_spectrum(gconv.pack_weight(to_dev(psi, dt)))
+    y_ref = ops.forward(gconv.gather(ft, T, k), wspec, bt, T, k * k * Cin, Cout).view(B, H, W, Cout, T)
+    assert torch.equal(gconv.forward_implicit(ft, wspec, bt, T, Cout, k), y_ref)
+
+
 def test_implicit_gather_refuses_unaligned_channels():
     from paper_2607_21271_amd import _lib, gconv, ops
     f = torch.zeros(1, 4, 4, 3, 4, device="cuda")

@@ -200,30 +200,29 @@ def test_autograd_module_matches_oracle(orc):
     assert rel_err(m.bias.grad.cpu().numpy(), ref_db) <= 1e-5
 
 
-# The weight mode is chosen from the shape and the row count; each mode is also
-# forced here on small inputs so that both instantiations of a shape stay under
-# test (0: streamed weights, 2: every weight block resident in LDS, where the
-# blocks fit; elsewhere the plan keeps its own mode).
+# The plan is chosen from the shape and the row count; two others are forced here
+# on small inputs, valid in both directions of every shape (chunks of six steps,
+# or all at once, in two output splits; chunks of two steps in three).
 FORCED = [(3, 64, 64, 1029, True), (4, 24, 96, 2085, False), (4, 96, 24, 700, False),
           (5, 64, 64, 515, True), (8, 48, 48, 613, True), (12, 64, 64, 257, True),
           (7, 40, 72, 130, False), (2, 64, 200, 99, True), (8, 96, 384, 300, False)]
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("mode", ["0", "2"])
+@pytest.mark.parametrize("plan", ["1,4,2,6", "1,8,3,2"])
 @pytest.mark.parametrize("dt", ["f32", "f16"])
 @pytest.mark.parametrize("T,Cin,Cout,N,bias", FORCED,
                          ids=["T%d-%dx%d-N%d" % f[:4] for f in FORCED])
-def test_forced_weight_mode(orc, monkeypatch, T, Cin, Cout, N, bias, dt, mode):
-    say("forced mode", mode, T, Cin, Cout, N, dt)
-    monkeypatch.setenv("EQL_GEMM_MODE", mode)
+def test_forced_plan(orc, monkeypatch, T, Cin, Cout, N, bias, dt, plan):
+    say("forced plan", plan, T, Cin, Cout, N, dt)
+    monkeypatch.setenv("EQL_XS_PLAN", plan)
     inp = synth.draw(T, Cin, Cout, N, bias, 7000 + 31 * T + Cin + Cout).rounded(dt)
     g = run_gpu(inp, dt, want=("y", "dx"))
     errs = {"y": rel_err(g["y"], orc.forward(inp.x, inp.w, inp.b)),
             "dx": rel_err(g["dx"], orc.backward_input(inp.dy, inp.w))}
     say("  ", {k: "%.2e" % v for k, v in errs.items()})
     for k, v in errs.items():
-        assert v <= TOL[dt], (T, Cin, Cout, dt, mode, k, v)
+        assert v <= TOL[dt], (T, Cin, Cout, dt, plan, k, v)
 
 
 # The weight-gradient reduction reads IPW consecutive partial items per plane
@@ -274,11 +273,9 @@ def test_weight_spectrum_unaligned_base(T, Cin, Cout, dt):
     assert torch.equal(a.cpu(), b.cpu())
 
 
-# Layers whose contraction fits in at most three MFMA steps and whose output
-# spans several o-chunks run the resident-spectrum mode (the activation
-# spectrum of a round stays in registers across o-chunks); covered across
-# group orders, both passes (the input gradient of the Cin > Cout cases), odd
-# and even o-chunk counts and one to three contraction steps.
+# Few contraction steps and many output tiles (a wave runs several tiles over the
+# one staged spectrum), across group orders and both passes (the input gradient
+# of the Cin > Cout cases), odd and even tile counts.
 RES_CASES = [(8, 96, 384, 300, False), (8, 40, 200, 333, True), (8, 384, 96, 260, True),
              (4, 24, 200, 517, False), (4, 200, 24, 300, True), (3, 64, 400, 1029, True),
              (5, 48, 300, 260, True), (7, 32, 256, 130, False), (6, 64, 200, 200, True),
@@ -289,8 +286,8 @@ RES_CASES = [(8, 96, 384, 300, False), (8, 40, 200, 333, True), (8, 384, 96, 260
 @pytest.mark.parametrize("dt", ["f32", "f16"])
 @pytest.mark.parametrize("T,Cin,Cout,N,bias", RES_CASES,
                          ids=["T%d-%dx%d-N%d" % f[:4] for f in RES_CASES])
-def test_resident_spectrum_mode(orc, T, Cin, Cout, N, bias, dt):
-    say("resident spectrum", T, Cin, Cout, N, dt)
+def test_many_output_tiles(orc, T, Cin, Cout, N, bias, dt):
+    say("many output tiles", T, Cin, Cout, N, dt)
     inp = synth.draw(T, Cin, Cout, N, bias, 7900 + 31 * T + Cin + Cout).rounded(dt)
     g = run_gpu(inp, dt, want=("y", "dx"))
     errs = {"y": rel_err(g["y"], orc.forward(inp.x, inp.w, inp.b)),
@@ -396,4 +393,4 @@ def test_wgrad_kernel_forced(orc, monkeypatch, T, Cin, Cout, N, bias, dt, mode):
         errs["db"] = rel_err(g["db"], ref_db)
     say("  ", {k: "%.2e" % v for k, v in errs.items()})
     for k, v in errs.items():
-        assert v <= TOL[dt], (T, Cin, Cout, dt, mode, k, v)
+        assert v <= TOL[dt], (T, Cin, Cout, dt, plan, k, v)
