@@ -114,7 +114,7 @@ constexpr int attn_k_pitch(int D) { return D * 2 + 16; }
 constexpr int attn_v_pitch(int KT) { return KT * 64 + 16; }
 constexpr int attn_lds_bytes(int D, int KT) { return KT * 32 * attn_k_pitch(D) + D * attn_v_pitch(KT); }
 
-// waves of a workgroup: two workgroups fit a CU's LDS at the long sequences
+// waves of a workgroup: at the long sequences one or two workgroups fit a CU's LDS
 constexpr int attn_waves(int KT) { return KT > 4 ? 8 : 4; }
 
 template <int DT, int D, int KT>

@@ -48,9 +48,12 @@ hipError_t attn_kt(const void* qkv, void* o, int64_t B, int L, int H, float scal
       const hipError_t e = hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
       if (e != hipSuccess) return e;
     }
-    // Two workgroups fit a CU: with fewer (image, head) pairs the query tiles of
-    // one are split, each part staging K and V again.
-    int64_t qs = (2 * (int64_t)cus + B * H - 1) / (B * H);
+    // With fewer (image, head) pairs than workgroups fit the device, the query tiles
+    // of one are split, each part staging K and V again.  Two workgroups fit a
+    // CU, one where K and V^T take more than half its LDS (head_dim 128 past 128
+    // tokens: 390 pairs of 150 tokens, fp16, in two parts 37 us, in one 28).
+    constexpr int resident = 2 * lds <= kLdsBytes ? 2 : 1;
+    int64_t qs = (resident * (int64_t)cus + B * H - 1) / (B * H);
     const int max_qs = ((L + 15) / 16 + attn_waves(KT) - 1) / attn_waves(KT);
     if (qs > max_qs) qs = max_qs;
     const int64_t most = launch_blocks(attn_waves(KT) * 64) / (H * qs);  // images of one launch
