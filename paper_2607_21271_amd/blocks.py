@@ -82,6 +82,12 @@ def _inference(*ts) -> bool:
     kernels: plain tensors of one supported type on the current GPU, whole
     16-byte words, and nothing that wants to see torch's own operations (a
     gradient, autocast, tracing, a transform, a dispatch mode)."""
+    if (torch.jit.is_tracing() or torch.compiler.is_compiling() or torch.is_autocast_enabled()
+            or torch._C._functorch.peek_interpreter_stack() is not None
+            or torch.autograd.forward_ad._current_level >= 0
+            or torch._C._len_torch_dispatch_stack() > 0
+            or torch._C._len_torch_function_stack() > 0):
+        return False
     x = ts[0]
     if not (x.is_cuda and x.dtype in _DT and x.numel() > 0 and x.device.index == torch.cuda.current_device()):
         return False
@@ -91,11 +97,7 @@ def _inference(*ts) -> bool:
             return False
         if t.requires_grad and torch.is_grad_enabled():
             return False
-    return not (torch.is_autocast_enabled() or torch.jit.is_tracing() or torch.compiler.is_compiling()
-                or torch._C._functorch.peek_interpreter_stack() is not None
-                or torch.autograd.forward_ad._current_level >= 0
-                or torch._C._len_torch_dispatch_stack() > 0
-                or torch._C._len_torch_function_stack() > 0)
+    return True
 
 
 class GroupLayerNorm(torch.nn.Module):

@@ -23,6 +23,23 @@ def _need_gpu():
         pytest.skip("no GPU")
 
 
+@pytest.fixture
+def ran(monkeypatch):
+    """Launches of the two kernels by the modules of blocks.py: {"norm": n, "attention": n}."""
+    from paper_2607_21271_amd import _lib
+    count = {"norm": 0, "attention": 0}
+
+    def counted(name, f):
+        def call(*a):
+            count[name] += 1
+            return f(*a)
+        return call
+
+    monkeypatch.setattr(_lib, "eqlinear_group_norm", counted("norm", _lib.eqlinear_group_norm))
+    monkeypatch.setattr(_lib, "eqlinear_attention", counted("attention", _lib.eqlinear_attention))
+    return count
+
+
 def _err(a, b):
     return float((a.double() - b).abs().max() / b.abs().max())
 
@@ -30,7 +47,7 @@ def _err(a, b):
 @pytest.mark.parametrize("T,C,rows", [(1, 8, 1), (3, 8, 5), (4, 192, 1001), (8, 96, 197), (5, 72, 70), (2, 1024, 9),
                                       (4, 257 * 2, 33), (16, 128, 8200), (4, 1024, 515), (8, 512, 7)])
 @pytest.mark.parametrize("dt", ["f32", "f16", "bf16"])
-def test_group_norm(T, C, rows, dt):
+def test_group_norm(ran, T, C, rows, dt):
     from paper_2607_21271_amd.blocks import GroupLayerNorm
     say("group norm", T, C, rows, dt)
     torch.manual_seed(T * C)
@@ -44,9 +61,9 @@ def test_group_norm(T, C, rows, dt):
         mu = xd.mean((-2, -1), keepdim=True)
         var = (xd - mu).square().mean((-2, -1), keepdim=True)
         ref = (xd - mu) / (var + m.eps).sqrt() * m.weight.double()[:, None] + m.bias.double()[:, None]
-    assert y.dtype == x.dtype and _err(y, ref) <= TOL[dt]
+    assert y.dtype == x.dtype and _err(y, ref) <= TOL[dt] and ran["norm"] == 1
     # a call that wants gradients takes torch's operations
-    assert m(x.clone().requires_grad_(True)).requires_grad
+    assert m(x.clone().requires_grad_(True)).requires_grad and ran["norm"] == 1
 
 
 @pytest.mark.parametrize("shape", [(1,), (192, 1), (1, 192)])
@@ -77,9 +94,9 @@ def test_group_norm_affine_of_another_shape(shape):
 @pytest.mark.parametrize("B,L,heads,D", [(1, 1, 1, 64), (2, 16, 3, 64), (1, 17, 2, 32), (3, 32, 1, 128), (2, 33, 5, 64),
                                          (1, 50, 12, 64), (2, 65, 3, 32), (1, 128, 2, 128), (1, 129, 2, 64),
                                          (5, 145, 6, 64), (50, 197, 12, 64), (1, 224, 3, 128), (2, 225, 2, 32),
-                                         (1, 256, 3, 64), (1, 256, 1, 128)])
+                                         (1, 256, 3, 64), (1, 256, 1, 128), (60, 130, 5, 128)])
 @pytest.mark.parametrize("dt", ["f16", "bf16"])
-def test_attention(B, L, heads, D, dt):
+def test_attention(ran, B, L, heads, D, dt):
     from paper_2607_21271_amd.blocks import EQViTBlock
     say("attention", B, L, heads, D, dt)
     torch.manual_seed(L)
@@ -93,10 +110,10 @@ def test_attention(B, L, heads, D, dt):
         q, k, v = qkv.double().view(B, L, 3, heads, D).permute(2, 0, 3, 1, 4).contiguous()
         a = torch.softmax(q @ k.transpose(-1, -2).contiguous() * D ** -0.5, -1)
         ref = (a @ v).permute(0, 2, 1, 3).reshape(B, L, C, T)
-    assert o.shape == ref.shape and _err(o, ref) <= TOL[dt]
+    assert o.shape == ref.shape and _err(o, ref) <= TOL[dt] and ran["attention"] == 1
 
 
-def test_attention_infinities():
+def test_attention_infinities(ran):
     """A query whose scores hold an infinity or a NaN gives NaN, its neighbours are untouched."""
     from paper_2607_21271_amd.blocks import EQViTBlock
     say("attention infinities")
@@ -112,4 +129,110 @@ def test_attention_infinities():
     hit = torch.zeros(1, 21, 32, 4, dtype=torch.bool, device="cuda")
     hit[0, 5, :16] = True
     hit[0, 9, 16:] = True
-    assert bool(o[hit].isnan().all()) and torch.equal(o[~hit], ref[~hit])
+    assert bool(o[hit].isnan().all()) and torch.equal(o[~hit], ref[~hit]) and ran["attention"] == 2
+
+
+class _Seen(torch.utils._python_dispatch.TorchDispatchMode):
+    def __init__(self):
+        super().__init__()
+        self.ops = 0
+
+    def __torch_dispatch__(self, func, types, args=(), kwargs=None):
+        self.ops += 1
+        return func(*args, **(kwargs or {}))
+
+
+def _norm_and_attention():
+    from paper_2607_21271_amd.blocks import EQViTBlock
+    torch.manual_seed(1)
+    blk = EQViTBlock(4, 32, 2, linear="standard", device="cuda", dtype=torch.float16)
+    x = torch.randn(3, 21, 32, 4, device="cuda").to(torch.float16)
+    qkv = torch.randn(3, 21, 96, 4, device="cuda").to(torch.float16)
+    return blk, x, qkv
+
+
+@pytest.mark.parametrize("how", ["autocast", "vmap", "forward_ad", "trace", "dispatch_mode", "strided", "misaligned",
+                                 "subclass", "weight_dtype"])
+def test_calls_that_keep_torchs_operations(ran, how):
+    """Where something wants to see torch's own operations, or the tensor is not the kernel's, no kernel is launched and
+    the result is torch's."""
+    blk, x, qkv = _norm_and_attention()
+    with torch.no_grad():
+        n0, a0 = blk.norm1(x), blk.attention(qkv)
+        ran.update(norm=0, attention=0)
+        if how == "autocast":
+            with torch.autocast("cuda", dtype=torch.float16):
+                n, a = blk.norm1(x), blk.attention(qkv)
+        elif how == "vmap":
+            n, a = torch.vmap(blk.norm1)(x), torch.vmap(lambda q: blk.attention(q[None])[0])(qkv)
+        elif how == "forward_ad":
+            with torch.autograd.forward_ad.dual_level():
+                d = torch.autograd.forward_ad.make_dual(x, torch.ones_like(x))
+                n, tangent = torch.autograd.forward_ad.unpack_dual(blk.norm1(d))
+                a = blk.attention(qkv)
+                assert tangent is not None
+        elif how == "trace":
+            n = torch.jit.trace(blk.norm1, x)(x)
+            a = torch.jit.trace(lambda q: blk.attention(q), qkv)(qkv)
+        elif how == "dispatch_mode":
+            with _Seen() as seen:
+                n, a = blk.norm1(x), blk.attention(qkv)
+            assert seen.ops > 10
+        elif how == "strided":
+            n = blk.norm1(x.transpose(0, 1).contiguous().transpose(0, 1))
+            a = a0  # (a strided qkv is refused by its view, as without the kernel)
+            with pytest.raises(RuntimeError):
+                blk.attention(qkv.transpose(2, 3).contiguous().transpose(2, 3))
+        elif how == "misaligned":
+            shift = lambda t: torch.cat([t.new_zeros(1), t.flatten()])[1:].view(t.shape)
+            n, a = blk.norm1(shift(x)), blk.attention(shift(qkv))
+        elif how == "subclass":
+            sub = type("Sub", (torch.Tensor,), {})
+            n, a = blk.norm1(x.as_subclass(sub)).as_subclass(torch.Tensor), blk.attention(qkv.as_subclass(sub)).as_subclass(torch.Tensor)
+        else:
+            blk.norm1.weight.data = blk.norm1.weight.data.float()
+            n, a = blk.norm1(x), a0
+    assert ran == {"norm": 0, "attention": 0}
+    assert _err(n, n0.double()) <= TOL["f16"] and _err(a, a0.double()) <= 2 * TOL["f16"]
+
+
+def test_kernels_run_on_the_current_stream(ran):
+    """On a side stream the launches wait for that stream's work: the input is written there by a long chain before
+    them, and read back from there."""
+    blk, x, qkv = _norm_and_attention()
+    with torch.no_grad():
+        n0, a0 = blk.norm1(x), blk.attention(qkv)
+        side = torch.cuda.Stream()
+        side.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.stream(side):
+            big = torch.ones(4096, 4096, device="cuda")
+            for _ in range(8):
+                big = big @ big * 2.0 ** -12
+            z = (big[0, 0] - 1.0).to(torch.float16)
+            n, a = blk.norm1(x + z), blk.attention(qkv + z)
+        torch.cuda.current_stream().wait_stream(side)
+    assert torch.equal(n, n0) and torch.equal(a, a0) and ran == {"norm": 2, "attention": 2}
+
+
+@pytest.mark.parametrize("dt", ["f16", "bf16"])
+def test_whole_block_inference(ran, dt):
+    """A 16-bit block without gradients runs both norms and the attention as kernels; against the same weights in
+    float64 through the unrolled layers, no further off than torch's operations at the same precision."""
+    from paper_2607_21271_amd.blocks import EQViTBlock
+    torch.manual_seed(9)
+    T, C, heads = 4, 64, 4
+    naive = EQViTBlock(T, C, heads, linear="naive", device="cuda", dtype=DT[dt])
+    flash = EQViTBlock(T, C, heads, linear="flash", device="cuda", dtype=DT[dt])
+    flash.copy_weights_from(naive)
+    ref = EQViTBlock(T, C, heads, linear="naive", dtype=torch.float64)
+    x = torch.randn(2, 50, C, T, device="cuda").to(DT[dt])
+    with torch.no_grad():
+        for a, b in zip(ref.parameters(), naive.parameters()):
+            a.copy_(b.double().cpu())
+        y = flash(x)
+        assert ran == {"norm": 2, "attention": 1}
+        with torch.enable_grad():
+            yt = flash(x.clone().requires_grad_(True)).detach()
+        assert ran == {"norm": 2, "attention": 1}
+        want = ref(x.double().cpu()).cuda()
+    assert _err(y, want) <= 1.5 * _err(yt, want)
