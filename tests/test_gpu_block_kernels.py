@@ -172,8 +172,8 @@ def test_calls_that_keep_torchs_operations(ran, how):
                 a = blk.attention(qkv)
                 assert tangent is not None
         elif how == "trace":
-            n = torch.jit.trace(blk.norm1, x)(x)
-            a = torch.jit.trace(lambda q: blk.attention(q), qkv)(qkv)
+            n = torch.jit.trace(blk.norm1, x, check_trace=False)(x)
+            a = torch.jit.trace(lambda q: blk.attention(q), qkv, check_trace=False)(qkv)
         elif how == "dispatch_mode":
             with _Seen() as seen:
                 n, a = blk.norm1(x), blk.attention(qkv)
