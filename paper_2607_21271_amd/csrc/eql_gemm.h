@@ -21,25 +21,14 @@ __device__ __forceinline__ void frag_mma(floatx4& acc, const Frag<KW*(DT != kF32
     const u32x4 bv = {b.w[0], b.w[1], b.w[2], b.w[3]};
     acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, av),
                                                  __builtin_bit_cast(half8, bv), acc, 0, 0, 0);
-  } else if constexpr (DT == kF16 && KW == 4) {
-    typedef _Float16 half4 __attribute__((ext_vector_type(4)));
-    const u32x2 av = {a.w[0], a.w[1]};
-    const u32x2 bv = {b.w[0], b.w[1]};
-    acc = __builtin_amdgcn_mfma_f32_16x16x16f16(__builtin_bit_cast(half4, av),
-                                                __builtin_bit_cast(half4, bv), acc, 0, 0, 0);
   } else if constexpr (DT == kBF16 && KW == 8) {
     typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
     const u32x4 av = {a.w[0], a.w[1], a.w[2], a.w[3]};
     const u32x4 bv = {b.w[0], b.w[1], b.w[2], b.w[3]};
     acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, av),
                                                   __builtin_bit_cast(bf16x8, bv), acc, 0, 0, 0);
-  } else if constexpr (DT == kBF16 && KW == 4) {
-    typedef short short4v __attribute__((ext_vector_type(4)));
-    const u32x2 av = {a.w[0], a.w[1]};
-    const u32x2 bv = {b.w[0], b.w[1]};
-    acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(short4v, av),
-                                                    __builtin_bit_cast(short4v, bv), acc, 0, 0, 0);
   } else {
+    static_assert(DT == kF32, "16-bit fragments hold eight channels a lane");
 #pragma unroll
     for (int s = 0; s < KW; ++s)
       acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__builtin_bit_cast(float, a.w[s]),
@@ -67,20 +56,10 @@ __device__ __forceinline__ int wl_off(int row, int byte) {
 
 template <int FB, int RB>
 __device__ __forceinline__ Frag<FB> lds_frag(const char* base, int row, int g) {
+  static_assert(FB == 16, "fragment size");
   Frag<FB> f;
-  if constexpr (FB == 32) {
-    const u32x4 a = *reinterpret_cast<const u32x4*>(base + wl_off<RB>(row, g * 32));
-    const u32x4 b = *reinterpret_cast<const u32x4*>(base + wl_off<RB>(row, g * 32 + 16));
-    f.w[0] = a[0]; f.w[1] = a[1]; f.w[2] = a[2]; f.w[3] = a[3];
-    f.w[4] = b[0]; f.w[5] = b[1]; f.w[6] = b[2]; f.w[7] = b[3];
-  } else if constexpr (FB == 16) {
-    const u32x4 a = *reinterpret_cast<const u32x4*>(base + wl_off<RB>(row, g * 16));
-    f.w[0] = a[0]; f.w[1] = a[1]; f.w[2] = a[2]; f.w[3] = a[3];
-  } else {
-    static_assert(FB == 8, "fragment size");
-    const u32x2 a = *reinterpret_cast<const u32x2*>(base + wl_off<RB>(row, g * 8));
-    f.w[0] = a[0]; f.w[1] = a[1];
-  }
+  const u32x4 a = *reinterpret_cast<const u32x4*>(base + wl_off<RB>(row, g * 16));
+  f.w[0] = a[0]; f.w[1] = a[1]; f.w[2] = a[2]; f.w[3] = a[3];
   return f;
 }
 
