@@ -28,8 +28,9 @@ inline WspecDims wspec_dims(int Cin, int Cout) {
 }
 
 // Plan of eql_xs_kernel for Ci -> Co over N rows: row tiles per workgroup,
-// waves, output splits, steps, steps staged at once (all of them, or an even
-// chunk with at most NW output tiles per split) and the LDS.
+// waves, output splits, steps, steps staged at once (all of them, an even chunk
+// with at most NW output tiles per split, or, pipelined, any chunk with fewer
+// output tiles than waves) and the LDS.
 enum XsForm { kXsWhole = 0, kXsChunk = 1, kXsPipe = 2 };
 struct XsPlan {
   int RT, NW, osplit, nks, kc, lds_bytes;
@@ -256,8 +257,16 @@ hipError_t launch_gemm(int dt, int T, bool bwd, const GemmArgs& a);
 // contraction channels a multiple of 32, and every 128-row tile of the input
 // and output below 2^31 bytes.  Taken by default for wide layers (both
 // channel counts at least kBigMinC), where the spectral products bound the
-// pass; EQL_GEMM_BIG=0 never takes it, =1 whenever the shape allows (tests,
-// A/B timing).
+// pass.  Against eql_xs_kernel (us, eql_xs_kernel / large tiles, forward, inputs
+// from HBM) the line is right at T = 4 for many rows and 512 channels or more
+// (fp16 1024 x 1024, 32,768 rows 566 / 435; 4,096 rows 84 / 58; 512 x 512, 8,192
+// rows 47 / 35; bf16 1024 x 1024, 32,768 rows 592 / 487), level at 256 x 256 in 16
+// bits (44 / 46 at 32,768 rows), and wrong where the tiles cannot fill the device
+// or the spectrum is small: few rows (fp16 1024 x 1024, 512 rows 16 / 47; fp32
+// 256 x 256, 512 rows 12 / 73), 256 x 1024 (fp16, 32,768 rows 129 / 168), fp32 at
+// 256 channels (32,768 rows 207 / 231) and T = 2 up to 1024 channels (fp16 1024 x
+// 1024, 32,768 rows 230 / 313).  EQL_GEMM_BIG=0 never takes it, =1 whenever the shape
+// allows (tests, A/B timing).
 struct BigArgs {
   const void* in;
   const void* wsp;   // plane block of the layout this pass reads
