@@ -26,9 +26,10 @@ def _need_gpu():
         pytest.skip("no GPU")
 
 
-# (layer, dtype, rows): a resident-spectrum forward, a ragged odd-T case with
-# bias, and an fp32 case with bias
-CASES = [("vit_b_mlp_up", "f16", 1500), ("sweep_T3", "f16", 777), ("vit_s_proj", "f32", 1037)]
+# (layer, dtype, rows): few rows of many output tiles, enough rows that the input
+# gradient is pipelined, a ragged odd-T case with bias, and an fp32 case with bias
+CASES = [("vit_b_mlp_up", "f16", 1500), ("vit_b_mlp_up", "f16", 8300), ("sweep_T3", "f16", 777),
+         ("vit_s_proj", "f32", 1037)]
 
 
 def _step(ops, x, w, b, dy, bufs, T, Cin, Cout, stream):
