@@ -208,15 +208,19 @@ XsPlan xs_plan(int64_t N, int T, int Ci, int Co, int dt, int cus) {
     int rt = rt_max;
     if (!w16 && kb >= 24 && T <= 4) rt = 1;
     // (T = 8, 48 -> 32, 111,648 rows 96 / 78; 37 -> 48, 117,087 rows 138 / 99)
-    if (!w16 && ((T >= 5 && n_ot <= 3 && (T < 8 || p.nks > 1)) || (T <= 4 && n_ot <= 2 && kb >= 8))) rt = 1;
-    // a spectrum of few KB and little work a row: four row tiles, one or two
+    if (!w16 && (T <= 4 ? n_ot <= 2 && kb >= 8
+                        : (T < 7 || p.nks > 1) && (n_ot <= 2 || (n_ot == 3 && kb <= 32))))
+      rt = 1;
+    // one step of few planes and little work a row: four row tiles, one or two
     // waves (T = 1, 8 -> 32, 304,390 rows, bf16, four waves 17.5 / 11.4; T = 2, 16 ->
     // 32, 164,161 rows, fp16, two row tiles and waves 13.3 / 11.5)
-    const bool tiny = T <= 2 && kb <= 4 && n_ot <= 2;
+    const bool tiny = T <= 2 && n_ot <= 2 && (p.nks == 1 || (!w16 && T == 1 && p.nks == 2));
     if (n_ot <= 2 && rt > 1 && !tiny) rt = kb <= 24 ? 2 : 1;  // little to share: more, smaller workgroups
     // (two at any N with many output tiles: T = 8, 256 -> 512, 12,000 rows 82 / 70;
-    // T = 4, 48 -> 1125, 11,789 rows 39 / 35; 96 -> 768, 9,000 rows 27 / 24)
-    const bool keep2 = w16 && ((T > 4 && n_ot > 16 && kb > 50) || (T >= 4 && n_ot >= 40));
+    // T = 4, 48 -> 1125, 11,789 rows 39 / 35; 96 -> 768, 9,000 rows 27 / 24; but not
+    // of one step: T = 8, 19 -> 752, 12,198 rows 31 / 34)
+    const bool keep2 =
+        w16 && ((T > 4 && n_ot > 16 && kb > 50) || ((T == 4 || T == 8) && n_ot >= 40 && p.nks > 1));
     while (rt > 1 && N < (int64_t)24 * rt * cus * (w16 ? 1 : 2) && !(rt == 2 && keep2)) rt /= 2;
     // KB of spectrum staged at once at most, as it is and with half the row
     // tiles.  16-bit layers of many output tiles read each staged row so often
@@ -231,12 +235,12 @@ XsPlan xs_plan(int64_t N, int T, int Ci, int Co, int dt, int cus) {
     // rows 41 / 33; over 340 layers of T = 1 .. 4, 48 to 640 channels, the whole
     // spectrum 1.12, these 1.03 times the best plan).
     const bool wide = w16 && T <= 8;
-    const int whole = n_ot <= 2 ? (w16 || T > 8 ? 52 : T > 4 ? 32 : 16)
+    const int whole = n_ot <= 2 ? (w16 || T > 4 ? 52 : 16)
                       : T > 8   ? (n_ot <= 4 ? 64 : 100)
                       : n_ot < 8 ? 64
                       : wide && (n_ot > 16 || (rt == 2 && n_ot > 12)) ? 128 : 100;
     const int half = n_ot <= 2 || (n_ot > 8 && !wide) ? 0 : n_ot > 12 && T > 1 ? 128 : 64;
-    const bool halve = rt * kb > whole && rt > (w16 ? 2 : 1) && rt / 2 * kb <= half;
+    const bool halve = rt * kb > whole && rt > (w16 || n_ot == 3 ? 2 : 1) && rt / 2 * kb <= half;
     if (rt * kb <= whole || halve) {
       if (halve) rt /= 2;
       const int lds = rt * kb;
@@ -250,14 +254,16 @@ XsPlan xs_plan(int64_t N, int T, int Ci, int Co, int dt, int cus) {
       // 81, 124,093 rows, fp32, three / four 190 / 173.
       if (n_ot <= 2) p.NW = lds < 20 ? 2 : 3;
       else if (n_ot == 3) p.NW = 3;
-      else if ((n_ot == 5 || n_ot == 6) && lds <= (w16 ? 36 : 24))
-        p.NW = (rt == 4 || !w16) && lds <= 16 && (N + 63) / 64 >= 8 * (int64_t)cus ? 2 : 3;
-      else if (w16 && rt == 4 && n_ot >= 24 && Co % 16 != 0) p.NW = 8;
-      if (!w16 && n_ot <= 2 && T >= 5) p.NW = T > 8 && kb > 28 && N >= 64 * (int64_t)cus ? 4 : 2;
+      else if ((n_ot == 5 || n_ot == 6) && lds <= (w16 || T > 4 ? 36 : 24))
+        p.NW = (rt == 4 || (!w16 && lds > 8)) && lds <= 16 && (N + 63) / 64 >= 8 * (int64_t)cus ? 2 : 3;
+      else if (w16 && rt == 4 && n_ot >= 24 && Co % 16 != 0 && T % 2 == 0) p.NW = 8;
+      if (!w16 && T >= 5 && (n_ot <= 2 || (n_ot == 3 && T > 8 && p.nks == 1)))
+        p.NW = T > 8 && T != 16 && kb > 28 && N >= 64 * (int64_t)cus && N < 256 * (int64_t)cus ? 4 : 2;
       if (tiny) p.NW = T == 1 || n_ot == 1 ? 1 : 2;
-      // one step and little work a row (T = 10, 16 -> 27, 89,862 rows 27.5 / 26.5; T =
+      // half a step and little work a row (T = 10, 16 -> 27, 89,862 rows 27.5 / 26.5; T =
       // 16, 16 -> 48, 31,534 rows, bf16, three / one 24.9 / 18.6)
-      if (T > 8 && p.nks == 1 && w16 && (T <= 12 ? n_ot <= 2 && N >= 256 * (int64_t)cus : n_ot == 3)) p.NW = 1;
+      if (T > 8 && w16 && Ci <= 16 && (T <= 12 ? n_ot <= 2 && N >= 256 * (int64_t)cus : n_ot == 3 && N >= 96 * (int64_t)cus))
+        p.NW = 1;
     } else if (n_ot <= 2) {
       p.NW = 2;
       p.kc = chunk(16, rt);
@@ -269,9 +275,10 @@ XsPlan xs_plan(int64_t N, int T, int Ci, int Co, int dt, int cus) {
       // 16,500 59 / 64).  Other 16-bit layers: two row tiles in four waves (T = 4, 384
       // -> 96, 25,216 rows, bf16, four row tiles in three waves 53 / 37; 288 -> 96
       // 41 / 31), four while one round holds them (T = 4, 576 -> 64, 25,088 rows 39 /
-      // 35; 35,088 rows 47 / 55), no idle fourth wave where all workgroups fit at
-      // once (T = 4, 384 -> 96, 12,608 rows 22 / 20).  fp32: one row tile, small
-      // chunks and splits of two or three tiles (T = 4, 384 -> 96, 25,216 rows 139 /
+      // 35; 35,088 rows 47 / 55) and for seven or eight tiles over many rows (T = 3, 322
+      // -> 112, 156,647 rows 163 / 150), no idle fourth wave where all workgroups fit at
+      // once (T = 4, 384 -> 96, 12,608 rows 22 / 20).  fp32: one row tile (two for
+      // three output tiles at T > 4), small chunks and splits of two or three tiles (T = 4, 384 -> 96, 25,216 rows 139 /
       // 120; T = 8, 384 -> 96, 12,608 rows 165 / 153; T = 4, 384 -> 96, 12,608 rows 77 / 67).
       const int64_t g64 = (N + 63) / 64, rounds = (g64 + cus - 1) / cus;
       if (xs_pipe_inst(T, w16, 4) && n_ot >= 5 && n_ot <= 6 && (rounds == 1 || 8 * g64 >= 5 * rounds * cus)) {
@@ -283,6 +290,8 @@ XsPlan xs_plan(int64_t N, int T, int Ci, int Co, int dt, int cus) {
         p.osplit = n_ot <= 4 ? 1 : 2;
         if (rt == 4 && n_ot <= 4 && g64 <= 2 * cus) {
           p.kc = chunk(64, rt);
+        } else if (rt == 4 && n_ot >= 7 && g64 >= 3 * cus) {
+          p.kc = chunk(40, rt);
         } else {
           if (rt > 2) rt = 2;
           p.kc = chunk(T == 1 ? 16 : 40, rt);
@@ -293,7 +302,7 @@ XsPlan xs_plan(int64_t N, int T, int Ci, int Co, int dt, int cus) {
         p.NW = (n_ot + p.osplit - 1) / p.osplit;
         p.kc = chunk(40, rt);
       } else {
-        rt = 1;
+        if (n_ot > 3 || T <= 4) rt = 1;
         p.osplit = n_ot <= 4 ? 1 : n_ot <= 6 && T >= 5 ? 3 : 2;
         p.NW = n_ot == 3 && T <= 4 ? 4 : (n_ot + p.osplit - 1) / p.osplit;
         p.kc = chunk(n_ot == 5 || n_ot == 6 ? (T >= 5 ? 16 : 24) : 32, rt);
