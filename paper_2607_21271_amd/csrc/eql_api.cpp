@@ -257,7 +257,8 @@ XsPlan xs_plan(int64_t N, int T, int Ci, int Co, int dt, int cus) {
       else if ((n_ot == 5 || n_ot == 6) && lds <= (w16 || T > 4 ? 36 : 24))
         p.NW = (rt == 4 || (!w16 && lds > 8)) && lds <= 16 && (N + 63) / 64 >= 8 * (int64_t)cus ? 2 : 3;
       else if (w16 && rt == 4 && n_ot >= 24 && Co % 16 != 0 && T % 2 == 0) p.NW = 8;
-      if (!w16 && T >= 5 && (n_ot <= 2 || (n_ot == 3 && T > 8 && p.nks == 1)))
+      // (three fp32 tiles over few rows: T = 8, 48 -> 48, 12,608 rows, three / two 18.4 / 17.9)
+      if (!w16 && T >= 5 && (n_ot <= 2 || (n_ot == 3 && ((T > 8 && p.nks == 1) || N < 64 * (int64_t)cus))))
         p.NW = T > 8 && T != 16 && kb > 28 && N >= 64 * (int64_t)cus && N < 256 * (int64_t)cus ? 4 : 2;
       if (tiny) p.NW = T == 1 || n_ot == 1 ? 1 : 2;
       // half a step and little work a row (T = 10, 16 -> 27, 89,862 rows 27.5 / 26.5; T =

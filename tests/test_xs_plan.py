@@ -66,6 +66,7 @@ def test_plans_meet_the_kernels_assumptions():
     (12608, 8, 192, 48, "f32", (1, 3, 1, 4, CHUNK)), (39284, 4, 155, 16, "f32", (1, 2, 1, 4, CHUNK)),
     # little work a row: few waves
     (304390, 1, 8, 32, "bf16", (4, 1, 1, 1, WHOLE)), (111648, 8, 48, 32, "f32", (1, 2, 1, 3, WHOLE)),
+    (12608, 8, 48, 48, "f32", (1, 2, 1, 3, WHOLE)),
     (401408, 4, 24, 96, "f32", (2, 2, 1, 2, WHOLE)), (401408, 4, 24, 96, "f16", (4, 2, 1, 1, WHOLE))])
 def test_measured_choices(N, T, Ci, Co, dt, want):
     p = plan(N, T, Ci, Co, dt)
